@@ -204,12 +204,12 @@ abm_status abm_autotune(abm_ctx *ctx, const abm_problem *probs, int32_t B, doubl
                         abm_tuning *best, abm_tune_trial *trials, int32_t max_trials,
                         int32_t *n_trials);
 
-/* One trajectory (problem 0 of a plan made with B = 1) by the plain per-step
- * method: every step's two history sums are split over workgroups that each
- * own a fixed slice of the history, reduced across the grid, and the
- * predictor/corrector update is taken redundantly by every workgroup (the
- * partition and single reduction per step of Algorithm 1, with the per-node
- * reduction of Algorithm 2 done by wavefronts).
+/* One trajectory (problem 0 of a plan made with B = 1), its history spread
+ * over workgroups that each own a fixed slice of it (the partition of
+ * Algorithm 1).  The reduction over them is taken once per block of 64 steps:
+ * one workgroup steps, adding the newest two blocks' terms itself, and
+ * receives the slices' sums of older history a block ahead.  (Double-double
+ * plans: one reduction and a redundant update per step, as in Algorithm 1.)
  * y_out: device pointer to n_out*d doubles, n_out = 1 (stride 0) or
  * N/stride + 1 (+1 if stride does not divide N), states in step order.
  * Errors: ABM_EINVAL (prob does not match the plan), ABM_EDEVICE. */
@@ -281,17 +281,18 @@ abm_status abm_poll(abm_ctx *ctx, uint64_t ticket, abm_result *res);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): abm_solve
- * without a plan.  One trajectory by the plain per-step method, on the
+ * without a plan.  One trajectory as abm_solve runs it, on the
  * current HIP device, enqueued on hip_stream (a hipStream_t; NULL = the null
  * stream), results bitwise those of abm_solve for the same problem.  prob and
  * y_out as for abm_solve (y_out: device memory of n_out*d doubles, owned by
  * the caller).  Allocates nothing: the weight tables, the status word and the
- * cooperative form's step flags and partial sums live in a library-wide
- * device array of 8 MiB that each GPU holds until the process ends.
+ * step flags live in a library-wide device array of 8 MiB, the partial sums
+ * of several workgroups in one of 4 MiB, which each GPU holds until the
+ * process ends.
  * Limit: (distinct orders among the components) * 3 * (N + 2048) * 8 bytes
  * plus about 130 KiB must fit those 8 MiB (one order: N <= 341952), and the plain
  * path's own limit applies; larger problems return ABM_EINVAL.  Calls on one
- * GPU share the array and keep the last call's contents: calls that overlap
+ * GPU share the arrays and keep the last call's contents: calls that overlap
  * on one GPU (different streams or host threads) race and must be serialised
  * by the caller; one stream orders them.  No plan means no abm_plan_check: a
  * run whose device-side wait gave up, or whose state became non-finite,

@@ -291,7 +291,7 @@ abm_status abm_plan_tuned(abm_ctx* ctx, const abm_problem* probs, int32_t B,
         // double-double: the plain path only, and it must fit
         st = plain_setup_dd(pl);
     } else if (st == ABM_OK && B == 1) {
-        // the plain path is optional: a history too long for it leaves plain_G = 0
+        // the plain path is optional: a history too long for it leaves plain_ok false
         const abm_status ps = plain_setup(pl);
         if (ps == ABM_ENOMEM || ps == ABM_EDEVICE) st = ps;
         if (ps != ABM_OK) pl->plain_error = abm_last_error();
@@ -357,7 +357,7 @@ abm_status abm_solve(abm_plan_t* pl, const abm_problem* prob, double* y_out)
 {
     if (!pl || !prob || !y_out) return fail(ABM_EINVAL, "NULL argument");
     if (pl->B != 1) return fail(ABM_EINVAL, "abm_solve needs a plan made for one problem (B=%d)", pl->B);
-    if (pl->plain_G <= 0) return fail(ABM_EINVAL, "plain path unavailable: %s", pl->plain_error.c_str());
+    if (!pl->plain_ok) return fail(ABM_EINVAL, "plain path unavailable: %s", pl->plain_error.c_str());
     abm_status s = validate(*prob, 0);
     if (s != ABM_OK) return s;
     if (!same_shape(*prob, pl->shape[0]))
@@ -373,15 +373,17 @@ abm_status abm_solve(abm_plan_t* pl, const abm_problem* prob, double* y_out)
         T.gam[i] = t.gam;
         T.alpha[i] = t.alpha;
     }
-    const PlainShape sh{pl->plain_single, pl->plain_G, pl->plain_nloc};
-    const PlainArgs A = plain_args(*prob, T, sh, pl->part, pl->flags, pl->status, y_out);
+    PlainArgs A = plain_args(*prob, T, pl->plain, pl->part, pl->flags, pl->status, y_out);
     const int kind = chain_kind(prob->rhs, orders_differ(*prob));
     if (pl->dd) {
-        if (!sh.single && (e = launch_fill_u32(A.flags, 0, sh.G, pl->ctx->stream)) != hipSuccess)
+        A.G = pl->plain_G;
+        A.nloc = pl->plain_nloc;
+        A.part = pl->part;
+        if (!pl->plain_single && (e = launch_fill_u32(A.flags, 0, A.G, pl->ctx->stream)) != hipSuccess)
             return hip_fail(e, "flag reset");
-        e = launch_plain_dd(A, sh.single, kind, pl->ctx->stream);
+        e = launch_plain_dd(A, pl->plain_single, kind, pl->ctx->stream);
     } else {
-        e = plain_enqueue(A, sh, kind, pl->ctx->stream);
+        e = plain_enqueue(A, pl->plain, kind, pl->ctx->stream);
     }
     if (e != hipSuccess) return hip_fail(e, "plain kernel launch");
     return ABM_OK;
@@ -391,37 +393,56 @@ abm_status abm_solve(abm_plan_t* pl, const abm_problem* prob, double* y_out)
 
 namespace abm {
 
+// Up to kAloneBlocks blocks workgroup 0 runs alone: the waves beside its
+// sequencer then keep up (2048 steps, us per step alone / with 2 workgroups:
+// linear 0.068 / 0.074, oscillator 0.119 / 0.117; 4096 steps: 0.091 / 0.067
+// and 0.150 / 0.107).  Beyond, a worker per kWorkerChunks chunks: fewer fall
+// behind the sequencer at the end of the run (200000-step oscillator, 46
+// chunks each: 0.111 against 0.100 us per step), more only add traffic on the
+// flags (linear, 65536 steps: 0.056 at 16 chunks each, 0.063 at 8).
+constexpr int kAloneBlocks = 32;
+constexpr int kWorkerChunks = 16;
+
 abm_status plain_shape(const abm_problem& p, int n_cu, PlainShape* out)
 {
-    const int ch = plain_chunk();
-    const int64_t nchunks = std::max<int64_t>(1, (p.N + ch - 1) / ch);   // indices 0..N-1
-    const int nloc_max = plain_max_local_chunks(p.d);
-    // co-residency bound: one workgroup per CU is always possible for this kernel
-    const int gcap = std::min(n_cu, 256);
-    const int gmin = (int)((nchunks + nloc_max - 1) / nloc_max);
-    if (gmin > gcap)
+    const int d = p.d;
+    const int gcap = std::min(n_cu, 256);      // one workgroup per CU is always resident
+    // the longest history accepted: 256 rows of d values per chunk in the LDS
+    // of gcap workgroups
+    const int64_t rows_max = (int64_t)gcap * 256 * ((kPlainLds - 512 * (size_t)d) / ((size_t)2048 * d));
+    if ((p.N + 255) / 256 * 256 > rows_max)
         return fail(ABM_EINVAL, "N=%lld too long for the plain path (history does not fit the LDS of %d workgroups)",
                     (long long)p.N, gcap);
-    // a history that fits one CU runs in one workgroup with no grid
-    // synchronisation (unless a workgroup count is forced)
-    const int tables = orders_differ(p) ? p.d : 1;
-    int G = env_int("ABM_PLAIN_G", 0);
-    if (G <= 0 && plain_single_fits(p.N, p.d, tables)) {
-        *out = PlainShape{true, 1, 0};
+    const bool pc = orders_differ(p);
+    const int64_t chunks = (p.N + kPlainBlock - 1) / kPlainBlock;
+    const int forced = env_int("ABM_PLAIN_G", 0);
+    const bool fits = plain_chain_lds(d, pc, chunks, true) <= kPlainLds;
+    PlainShape sh{};
+    if (fits && (forced == 1 || (forced <= 0 && chunks <= kAloneBlocks))) {
+        *out = sh;
         return ABM_OK;
     }
-    // otherwise the fewest workgroups whose local chunks all fit the
-    // kernel's register prefetch (no weight load on a step's dependent path)
-    const int pref = plain_prefetch_chunks(tables);
-    if (G <= 0) G = (int)((nchunks + pref - 1) / pref);
-    G = std::max(G, gmin);
-    G = std::min(G, gcap);
-    *out = PlainShape{false, G, (int)((nchunks + G - 1) / G)};
+    int others = forced > 0 ? std::max(forced, 2) - 1 : 0;      // workers and reducers
+    if (others == 0) {
+        const int W = (int)std::min<int64_t>((chunks + kWorkerChunks - 1) / kWorkerChunks, gcap);
+        others = W <= kPlainFan ? W : W + (W + kPlainFan - 1) / kPlainFan;
+    }
+    others = std::min(others, gcap - 1);
+    sh.nred = others <= kPlainFan ? 0 : (others + kPlainFan) / (kPlainFan + 1);
+    sh.W = others - sh.nred;
+    const int64_t each = (chunks + sh.W - 1) / sh.W;
+    sh.nloc = (int)std::min<int64_t>(each, plain_worker_chunks(d));
+    sh.nspill = (int)(each - sh.nloc);
+    const size_t slot = (size_t)2 * d * kPlainBlock, chunk = (size_t)d * kPlainBlock;
+    sh.work_doubles = kPlainRing * chunk + kPlainSlots * (size_t)(sh.nred + sh.W) * slot +
+                      (size_t)sh.W * sh.nspill * chunk;
+    sh.flags = kPlainFlagPad + sh.W + sh.nred;
+    *out = sh;
     return ABM_OK;
 }
 
 PlainArgs plain_args(const abm_problem& prob, const PlainTables& T, const PlainShape& sh,
-                     double* part, uint32_t* flags, uint32_t* status, double* y_out)
+                     double* work, uint32_t* flags, uint32_t* status, double* y_out)
 {
     PlainArgs A{};
     for (int i = 0; i < 4; ++i) {
@@ -436,9 +457,17 @@ PlainArgs plain_args(const abm_problem& prob, const PlainTables& T, const PlainS
     A.h = prob.h;
     for (int i = 0; i < 8; ++i) A.p[i] = prob.p[i];
     A.N = prob.N;
-    A.G = sh.G;
+    A.W = sh.W;
+    A.nred = sh.nred;
     A.nloc = sh.nloc;
-    A.part = part;
+    A.nspill = sh.nspill;
+    if (sh.W > 0) {
+        const size_t slot = (size_t)2 * prob.d * kPlainBlock, chunk = (size_t)prob.d * kPlainBlock;
+        A.ring = work;
+        A.rpart = A.ring + kPlainRing * chunk;
+        A.part = A.rpart + kPlainSlots * (size_t)sh.nred * slot;
+        A.spill = A.part + kPlainSlots * (size_t)sh.W * slot;
+    }
     A.flags = flags;
     A.y_out = y_out;
     A.out_stride = prob.out_stride;
@@ -453,9 +482,10 @@ PlainArgs plain_args(const abm_problem& prob, const PlainTables& T, const PlainS
 
 hipError_t plain_enqueue(const PlainArgs& A, const PlainShape& sh, int kind, hipStream_t st)
 {
-    if (sh.single) return launch_plain_single(A, kind, st);
-    hipError_t e = launch_fill_u32(A.flags, 0, sh.G, st);
-    if (e != hipSuccess) return e;
+    if (sh.W > 0) {
+        hipError_t e = launch_fill_u32(A.flags, 0, sh.flags, st);
+        if (e != hipSuccess) return e;
+    }
     return launch_plain(A, kind, st);
 }
 
@@ -466,11 +496,12 @@ abm_status plain_setup_dd(abm_plan_s* pl)
     int G = env_int("ABM_PLAIN_G", 0);
     if (G <= 0 && plain_dd_single_fits(p.N, p.d, tables)) {
         pl->plain_single = true;
+        pl->plain_ok = true;
         pl->plain_G = 1;
         pl->plain_nloc = 0;
         return ABM_OK;
     }
-    const int ch = plain_chunk();
+    const int ch = kPlainChunkDD;
     const int64_t nchunks = std::max<int64_t>(1, (p.N + ch - 1) / ch);
     const int nloc_max = plain_dd_max_local_chunks(p.d);
     const int gcap = std::min(pl->ctx->n_cu, 256);
@@ -486,6 +517,7 @@ abm_status plain_setup_dd(abm_plan_s* pl)
     if (G <= 0) G = (int)std::max<int64_t>((nchunks + 3) / 4, std::min<int64_t>(nchunks, 32));
     G = std::min(std::max(G, gmin), gcap);
     pl->plain_single = false;
+    pl->plain_ok = true;
     pl->plain_G = G;
     pl->plain_nloc = (int)((nchunks + G - 1) / G);
     abm_status st = dev_alloc((void**)&pl->part, plain_dd_part_doubles(G) * sizeof(double),
@@ -496,15 +528,14 @@ abm_status plain_setup_dd(abm_plan_s* pl)
 
 abm_status plain_setup(abm_plan_s* pl)
 {
-    PlainShape sh{};
-    abm_status st = plain_shape(pl->shape[0], pl->ctx->n_cu, &sh);
+    abm_status st = plain_shape(pl->shape[0], pl->ctx->n_cu, &pl->plain);
     if (st != ABM_OK) return st;
-    pl->plain_single = sh.single;
-    pl->plain_G = sh.G;
-    pl->plain_nloc = sh.nloc;
-    if (sh.single) return ABM_OK;
-    st = dev_alloc((void**)&pl->part, plain_part_doubles(sh.G) * sizeof(double), "plain partials");
-    if (st == ABM_OK) st = dev_alloc((void**)&pl->flags, sh.G * sizeof(uint32_t), "plain flags");
+    const PlainShape& sh = pl->plain;
+    if (sh.W > 0) {
+        st = dev_alloc((void**)&pl->part, sh.work_doubles * sizeof(double), "plain workspace");
+        if (st == ABM_OK) st = dev_alloc((void**)&pl->flags, sh.flags * sizeof(uint32_t), "plain flags");
+    }
+    pl->plain_ok = st == ABM_OK;
     return st;
 }
 

@@ -25,9 +25,27 @@ constexpr int kRhsCount = 6;
 constexpr int kChainKinds = 2 * kRhsCount;
 inline int chain_kind(int rhs, bool per_comp) { return rhs + (per_comp ? kRhsCount : 0); }
 
-// ---- K1: plain per-step persistent kernel --------------------------------
+// ---- K1: one trajectory, blocks of 64 steps (plain_block.h) ----------------
+constexpr int kPlainBlock = 64;    // steps per block, history rows per chunk
+constexpr int kPlainSlots = 4;     // partial slots per worker, by block mod kPlainSlots
+constexpr int kPlainFan = 16;      // partials summed by one workgroup
+constexpr int kPlainRing = 8;      // published chunks kept
+constexpr int kPlainFlagPad = 32;  // flags[0]: workgroup 0's progress; the workers' flags start here
+constexpr size_t kPlainLds = 160 * 1024 - 256;   // LDS of one gfx950 CU, less the static flag
+
+// Launch shape: workgroup 0 steps, W workers hold the history (0: workgroup 0
+// alone), nred reducers sum the workers' partials in groups of kPlainFan.
+struct PlainShape {
+    int32_t W;
+    int32_t nred;
+    int32_t nloc;        // history chunks a worker keeps in LDS
+    int32_t nspill;      // and in device memory beyond them
+    size_t work_doubles; // device workspace: ring, reducers' and workers' slots, spilled chunks
+    int flags;           // uint32 flags, zero at launch
+};
+
 struct PlainArgs {
-    const double* b[4];  // weights b_k, k < N, of each component's order
+    const double* b[4];  // weights b_k, k < N + 128, of each component's order
     const double* a[4];  // weights a_k
     const double* c[4];  // weights c_k
     const double* gam[4];  // Gamma(alpha+1), Gamma(alpha+2)
@@ -37,31 +55,30 @@ struct PlainArgs {
     double x1[4];        // y'(0), used by components of order above 1
     double p[8];
     int64_t N;
-    int32_t G;           // workgroups (all co-resident)
-    int32_t nloc;        // history chunks held in LDS per workgroup
-    double* part;        // plain_part_doubles(G) doubles
-    uint32_t* flags;     // G step flags, zero at launch
+    int32_t G;           // double-double: workgroups (all co-resident)
+    int32_t W;           // PlainShape
+    int32_t nred;
+    int32_t nloc;
+    int32_t nspill;
+    double* ring;        // the last kPlainRing chunks
+    double* rpart;       // reducers' partial slots
+    double* part;        // workers' partial slots
+    double* spill;
+    uint32_t* flags;
     double* y_out;
     int64_t out_stride;
     uint32_t* status;    // device status word (kStatus* bits)
     uint32_t spin_limit; // bound on each device-side wait
-    uint32_t wait_bias;  // added to every awaited step number: 0 (a test hook
+    uint32_t wait_bias;  // added to every awaited number: 0 (a test hook
                          // sets it so that no wait can be met)
 };
-int plain_max_local_chunks(int d);
-int plain_chunk();
-// Local chunks per workgroup whose weights the kernel prefetches into
-// registers (tables: weight tables in use, 1 or d); beyond it, in-step loads.
-int plain_prefetch_chunks(int tables);
-int plain_part_doubles(int G);
-// kind: chain_kind(rhs, components have their own orders)
+// Bytes of LDS workgroup 0 needs for `chunks` chunks, and the chunks a worker
+// can keep.
+size_t plain_chain_lds(int d, bool per_comp, int64_t chunks, bool alone);
+int plain_worker_chunks(int d);
+// kind: chain_kind(rhs, components have their own orders).  One cooperative
+// launch (an ordinary one if A.W = 0); flags zero.
 hipError_t launch_plain(const PlainArgs& A, int kind, hipStream_t st);
-// The one-workgroup form (no grid synchronisation, weights held in registers)
-// for histories that fit one CU's LDS: whether N steps of d components with
-// the given number of weight tables fit it, and its launch (G, nloc, part and
-// flags of A are not used).
-bool plain_single_fits(int64_t N, int d, int tables);
-hipError_t launch_plain_single(const PlainArgs& A, int kind, hipStream_t st);
 
 // ---- K0 / K1 in double-double (ABM_FAR_DD) -----------------------------------
 // Tables of (hi, lo) pairs: gam holds Gamma(alpha+1), Gamma(alpha+2) (4 doubles),
@@ -69,6 +86,7 @@ hipError_t launch_plain_single(const PlainArgs& A, int kind, hipStream_t st);
 // receives 2d doubles per state.
 hipError_t launch_weights_dd(double alpha, int64_t n, double* gam, double* b, double* a, double* c,
                              hipStream_t st);
+constexpr int kPlainChunkDD = 256;
 bool plain_dd_single_fits(int64_t N, int d, int tables);
 int plain_dd_max_local_chunks(int d);
 int plain_dd_part_doubles(int G);

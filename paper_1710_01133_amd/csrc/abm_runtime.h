@@ -99,9 +99,11 @@ struct abm_plan_s {
     std::vector<int> table_of;    // [problem][component]: 4 entries per problem
     uint32_t* status = nullptr;
     // plain path (B == 1)
-    int plain_G = 0;
+    bool plain_ok = false;
+    abm::PlainShape plain{};
+    int plain_G = 0;              // double-double kernels' shape
     int plain_nloc = 0;
-    bool plain_single = false;    // the one-workgroup form (short histories)
+    bool plain_single = false;
     bool dd = false;              // double-double plan (ABM_FAR_DD): plain path only, tables
                                   // of (hi, lo) pairs
     std::string plain_error;
@@ -155,13 +157,6 @@ int env_int(const char* name, int dflt);
 abm_status dev_alloc(void** p, size_t bytes, const char* what);
 void dev_free(void* p);
 
-// Launch shape of the plain path for one problem: the one-workgroup form, or
-// G cooperative workgroups holding nloc history chunks each.
-struct PlainShape {
-    bool single;
-    int G;
-    int nloc;
-};
 // Weight tables of each component (all the same unless orders differ).
 struct PlainTables {
     const double* b[4];
@@ -172,8 +167,8 @@ struct PlainTables {
 };
 abm_status plain_shape(const abm_problem& p, int n_cu, PlainShape* out);
 PlainArgs plain_args(const abm_problem& prob, const PlainTables& T, const PlainShape& sh,
-                     double* part, uint32_t* flags, uint32_t* status, double* y_out);
-// flags reset (cooperative form) and the kernel, on st
+                     double* work, uint32_t* flags, uint32_t* status, double* y_out);
+// flags reset and the kernel, on st
 hipError_t plain_enqueue(const PlainArgs& A, const PlainShape& sh, int kind, hipStream_t st);
 abm_status plain_setup(abm_plan_s* pl);
 abm_status plain_setup_dd(abm_plan_s* pl);

@@ -1,15 +1,17 @@
-// abm_solve_noalloc: the plain per-step solve of one trajectory (as
-// abm_solve) for callers that cannot allocate device memory.  Everything the
-// kernels need beyond the caller's problem and output lives in `scratch`, a
-// file-scope device array each GPU holds until the process ends:
+// abm_solve_noalloc: the plain solve of one trajectory (as abm_solve) for
+// callers that cannot allocate device memory.  Everything the kernels need
+// beyond the caller's problem and output lives in two file-scope device
+// arrays each GPU holds until the process ends: `scratch`
 //
 //   [0, 256)            status word (kStatus* bits)
-//   [256, 1280)         step flags of the cooperative form (256 x uint32)
-//   [1280, 1280 + 32K)  partial slots of the cooperative form (2 x 256 x 8 doubles)
+//   [256, kTablesOff)   step flags
 //   then per distinct order: Gamma(alpha+1), Gamma(alpha+2) (256 B), then
-//   b, a, c, each N + kWeightPad doubles (256-byte aligned).
+//   b, a, c, each N + kWeightPad doubles (256-byte aligned)
 //
-// The host never uses the array's name as an address: the device address of
+// and `slots`, the ring of published chunks and the partial slots of the form
+// with several workgroups.
+//
+// The host never uses an array's name as an address: the device address of
 // each GPU's copy comes from hipGetSymbolAddress, taken once per device with
 // that device current, and that pointer is what the kernels receive.  Nothing
 // here allocates; the launches are the weight kernel, the fill kernel and the
@@ -30,33 +32,42 @@ namespace {
 constexpr size_t kScratchBytes = (size_t)8 << 20;
 constexpr size_t kStatusOff = 0;
 constexpr size_t kFlagsOff = 256;
-constexpr size_t kPartOff = 1280;
-constexpr size_t kTablesOff = kPartOff + 8 * 256 * 8 * sizeof(double);   // plain_part_doubles(256)
+constexpr size_t kTablesOff = 1280 + 128 * 1024;   // the stated limit on N follows from it
+constexpr size_t kSlotBytes = (size_t)4 << 20;     // 256 workgroups' slots of three components
 constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char slots[kSlotBytes];
+
+struct Arrays {
+    unsigned char* scratch;
+    unsigned char* slots;
+};
 
 std::mutex g_mu;
-unsigned char* g_ptr[kMaxDevices] = {};
+Arrays g_ptr[kMaxDevices] = {};
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-// This device's copy of scratch (the current device).
-abm_status scratch_of(int dev, unsigned char** out)
+// This device's copies (the current device).
+abm_status arrays_of(int dev, Arrays* out)
 {
     if (dev < 0 || dev >= kMaxDevices) return fail(ABM_EINVAL, "device %d", dev);
     std::lock_guard<std::mutex> lk(g_mu);
-    if (!g_ptr[dev]) {
+    if (!g_ptr[dev].slots) {
         void* p = nullptr;
-        const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+        hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
         if (e != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch)");
-        g_ptr[dev] = static_cast<unsigned char*>(p);
+        g_ptr[dev].scratch = static_cast<unsigned char*>(p);
+        e = hipGetSymbolAddress(&p, HIP_SYMBOL(slots));
+        if (e != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(slots)");
+        g_ptr[dev].slots = static_cast<unsigned char*>(p);
     }
     *out = g_ptr[dev];
     return ABM_OK;
 }
 
-// Workspace bytes one problem takes (status, flags, partials, its tables).
+// Bytes of scratch one problem takes (status, flags, its tables).
 size_t noalloc_bytes_needed(const abm_problem& p)
 {
     double seen[4];
@@ -97,10 +108,12 @@ extern "C" abm_status abm_solve_noalloc(const abm_problem* prob, double* y_out, 
     if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
     PlainShape sh{};
     if ((s = plain_shape(*prob, n_cu, &sh)) != ABM_OK) return s;
-    if ((size_t)plain_part_doubles(sh.G) * sizeof(double) > kTablesOff - kPartOff)
-        return fail(ABM_EINVAL, "%d workgroups' partial slots exceed the workspace layout", sh.G);
-    unsigned char* base = nullptr;
-    if ((s = scratch_of(dev, &base)) != ABM_OK) return s;
+    if (sh.work_doubles * sizeof(double) > kSlotBytes ||
+        kFlagsOff + sh.flags * sizeof(uint32_t) > kTablesOff)
+        return fail(ABM_EINVAL, "%d workgroups' partial slots exceed the workspace layout", sh.W);
+    Arrays arr_dev{};
+    if ((s = arrays_of(dev, &arr_dev)) != ABM_OK) return s;
+    unsigned char* const base = arr_dev.scratch;
     const hipStream_t st = (hipStream_t)hip_stream;
 
     // weight tables, one per distinct order (components of equal order share)
@@ -134,7 +147,7 @@ extern "C" abm_status abm_solve_noalloc(const abm_problem* prob, double* y_out, 
     uint32_t* status = reinterpret_cast<uint32_t*>(base + kStatusOff);
     if ((e = launch_fill_u32(status, 0, 1, st)) != hipSuccess) return hip_fail(e, "status reset");
     const PlainArgs A =
-        plain_args(*prob, T, sh, reinterpret_cast<double*>(base + kPartOff),
+        plain_args(*prob, T, sh, reinterpret_cast<double*>(arr_dev.slots),
                    reinterpret_cast<uint32_t*>(base + kFlagsOff), status, y_out);
     if ((e = plain_enqueue(A, sh, chain_kind(prob->rhs, orders_differ(*prob)), st)) != hipSuccess)
         return hip_fail(e, "plain kernel launch");
