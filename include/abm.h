@@ -208,8 +208,7 @@ abm_status abm_autotune(abm_ctx *ctx, const abm_problem *probs, int32_t B, doubl
  * over workgroups that each own a fixed slice of it (the partition of
  * Algorithm 1).  The reduction over them is taken once per block of 64 steps:
  * one workgroup steps, adding the newest two blocks' terms itself, and
- * receives the slices' sums of older history a block ahead.  (Double-double
- * plans: one reduction and a redundant update per step, as in Algorithm 1.)
+ * receives the slices' sums of older history a block ahead.
  * y_out: device pointer to n_out*d doubles, n_out = 1 (stride 0) or
  * N/stride + 1 (+1 if stride does not divide N), states in step order.
  * Errors: ABM_EINVAL (prob does not match the plan), ABM_EDEVICE. */

@@ -289,7 +289,7 @@ abm_status abm_plan_tuned(abm_ctx* ctx, const abm_problem* probs, int32_t B,
     }
     if (st == ABM_OK && dd) {
         // double-double: the plain path only, and it must fit
-        st = plain_setup_dd(pl);
+        st = plain_setup(pl);
     } else if (st == ABM_OK && B == 1) {
         // the plain path is optional: a history too long for it leaves plain_ok false
         const abm_status ps = plain_setup(pl);
@@ -373,18 +373,8 @@ abm_status abm_solve(abm_plan_t* pl, const abm_problem* prob, double* y_out)
         T.gam[i] = t.gam;
         T.alpha[i] = t.alpha;
     }
-    PlainArgs A = plain_args(*prob, T, pl->plain, pl->part, pl->flags, pl->status, y_out);
-    const int kind = chain_kind(prob->rhs, orders_differ(*prob));
-    if (pl->dd) {
-        A.G = pl->plain_G;
-        A.nloc = pl->plain_nloc;
-        A.part = pl->part;
-        if (!pl->plain_single && (e = launch_fill_u32(A.flags, 0, A.G, pl->ctx->stream)) != hipSuccess)
-            return hip_fail(e, "flag reset");
-        e = launch_plain_dd(A, pl->plain_single, kind, pl->ctx->stream);
-    } else {
-        e = plain_enqueue(A, pl->plain, kind, pl->ctx->stream);
-    }
+    const PlainArgs A = plain_args(*prob, T, pl->plain, pl->part, pl->flags, pl->status, y_out);
+    e = plain_enqueue(A, pl->plain, chain_kind(prob->rhs, orders_differ(*prob)), pl->dd, pl->ctx->stream);
     if (e != hipSuccess) return hip_fail(e, "plain kernel launch");
     return ABM_OK;
 }
@@ -406,17 +396,20 @@ constexpr int kWorkerChunks = 16;
 abm_status plain_shape(const abm_problem& p, int n_cu, PlainShape* out)
 {
     const int d = p.d;
+    const bool dd = p.far_prec == ABM_FAR_DD;
+    const int words = dd ? 2 : 1;
     const int gcap = std::min(n_cu, 256);      // one workgroup per CU is always resident
-    // the longest history accepted: 256 rows of d values per chunk in the LDS
-    // of gcap workgroups
-    const int64_t rows_max = (int64_t)gcap * 256 * ((kPlainLds - 512 * (size_t)d) / ((size_t)2048 * d));
+    // the longest history accepted: 256-row pieces in the LDS of gcap
+    // workgroups, less a fixed part
+    const size_t fixed = dd ? (size_t)1216 * d : (size_t)512 * d;
+    const int64_t rows_max = (int64_t)gcap * 256 * ((kPlainLds - fixed) / ((size_t)2048 * d * words));
     if ((p.N + 255) / 256 * 256 > rows_max)
-        return fail(ABM_EINVAL, "N=%lld too long for the plain path (history does not fit the LDS of %d workgroups)",
-                    (long long)p.N, gcap);
+        return fail(ABM_EINVAL, "N=%lld too long for the %splain path (history does not fit the LDS of %d workgroups)",
+                    (long long)p.N, dd ? "double-double " : "", gcap);
     const bool pc = orders_differ(p);
     const int64_t chunks = (p.N + kPlainBlock - 1) / kPlainBlock;
     const int forced = env_int("ABM_PLAIN_G", 0);
-    const bool fits = plain_chain_lds(d, pc, chunks, true) <= kPlainLds;
+    const bool fits = (dd ? plain_dd_chain_lds(d, pc, chunks, true) : plain_chain_lds(d, pc, chunks, true)) <= kPlainLds;
     PlainShape sh{};
     if (fits && (forced == 1 || (forced <= 0 && chunks <= kAloneBlocks))) {
         *out = sh;
@@ -431,9 +424,9 @@ abm_status plain_shape(const abm_problem& p, int n_cu, PlainShape* out)
     sh.nred = others <= kPlainFan ? 0 : (others + kPlainFan) / (kPlainFan + 1);
     sh.W = others - sh.nred;
     const int64_t each = (chunks + sh.W - 1) / sh.W;
-    sh.nloc = (int)std::min<int64_t>(each, plain_worker_chunks(d));
+    sh.nloc = (int)std::min<int64_t>(each, dd ? plain_dd_worker_chunks(d) : plain_worker_chunks(d));
     sh.nspill = (int)(each - sh.nloc);
-    const size_t slot = (size_t)2 * d * kPlainBlock, chunk = (size_t)d * kPlainBlock;
+    const size_t slot = (size_t)2 * d * kPlainBlock * words, chunk = (size_t)d * kPlainBlock * words;
     sh.work_doubles = kPlainRing * chunk + kPlainSlots * (size_t)(sh.nred + sh.W) * slot +
                       (size_t)sh.W * sh.nspill * chunk;
     sh.flags = kPlainFlagPad + sh.W + sh.nred;
@@ -462,7 +455,8 @@ PlainArgs plain_args(const abm_problem& prob, const PlainTables& T, const PlainS
     A.nloc = sh.nloc;
     A.nspill = sh.nspill;
     if (sh.W > 0) {
-        const size_t slot = (size_t)2 * prob.d * kPlainBlock, chunk = (size_t)prob.d * kPlainBlock;
+        const size_t chunk = (size_t)prob.d * kPlainBlock * (prob.far_prec == ABM_FAR_DD ? 2 : 1);
+        const size_t slot = 2 * chunk;
         A.ring = work;
         A.rpart = A.ring + kPlainRing * chunk;
         A.part = A.rpart + kPlainSlots * (size_t)sh.nred * slot;
@@ -480,50 +474,13 @@ PlainArgs plain_args(const abm_problem& prob, const PlainTables& T, const PlainS
     return A;
 }
 
-hipError_t plain_enqueue(const PlainArgs& A, const PlainShape& sh, int kind, hipStream_t st)
+hipError_t plain_enqueue(const PlainArgs& A, const PlainShape& sh, int kind, bool dd, hipStream_t st)
 {
     if (sh.W > 0) {
         hipError_t e = launch_fill_u32(A.flags, 0, sh.flags, st);
         if (e != hipSuccess) return e;
     }
-    return launch_plain(A, kind, st);
-}
-
-abm_status plain_setup_dd(abm_plan_s* pl)
-{
-    const abm_problem& p = pl->shape[0];
-    const int tables = orders_differ(p) ? p.d : 1;
-    int G = env_int("ABM_PLAIN_G", 0);
-    if (G <= 0 && plain_dd_single_fits(p.N, p.d, tables)) {
-        pl->plain_single = true;
-        pl->plain_ok = true;
-        pl->plain_G = 1;
-        pl->plain_nloc = 0;
-        return ABM_OK;
-    }
-    const int ch = kPlainChunkDD;
-    const int64_t nchunks = std::max<int64_t>(1, (p.N + ch - 1) / ch);
-    const int nloc_max = plain_dd_max_local_chunks(p.d);
-    const int gcap = std::min(pl->ctx->n_cu, 256);
-    const int gmin = (int)((nchunks + nloc_max - 1) / nloc_max);
-    if (gmin > gcap)
-        return fail(ABM_EINVAL, "N=%lld too long for the double-double plain path (history does not "
-                    "fit the LDS of %d workgroups)", (long long)p.N, gcap);
-    // four local chunks per workgroup: the most whose weights the kernel
-    // prefetches into registers (measured on the 200000-step oscillator:
-    // 6.3 us per step at 4 chunks, 7.1-7.3 at 5 to 8 with the weights loaded
-    // in the step); short histories spread over at least 32 workgroups while
-    // there are chunks for them (8192 steps: 2.39 us per step at 32, 2.55 at 8)
-    if (G <= 0) G = (int)std::max<int64_t>((nchunks + 3) / 4, std::min<int64_t>(nchunks, 32));
-    G = std::min(std::max(G, gmin), gcap);
-    pl->plain_single = false;
-    pl->plain_ok = true;
-    pl->plain_G = G;
-    pl->plain_nloc = (int)((nchunks + G - 1) / G);
-    abm_status st = dev_alloc((void**)&pl->part, plain_dd_part_doubles(G) * sizeof(double),
-                              "plain partials");
-    if (st == ABM_OK) st = dev_alloc((void**)&pl->flags, G * sizeof(uint32_t), "plain flags");
-    return st;
+    return dd ? launch_plain_dd(A, kind, st) : launch_plain(A, kind, st);
 }
 
 abm_status plain_setup(abm_plan_s* pl)

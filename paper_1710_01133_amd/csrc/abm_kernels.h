@@ -55,7 +55,6 @@ struct PlainArgs {
     double x1[4];        // y'(0), used by components of order above 1
     double p[8];
     int64_t N;
-    int32_t G;           // double-double: workgroups (all co-resident)
     int32_t W;           // PlainShape
     int32_t nred;
     int32_t nloc;
@@ -86,12 +85,9 @@ hipError_t launch_plain(const PlainArgs& A, int kind, hipStream_t st);
 // receives 2d doubles per state.
 hipError_t launch_weights_dd(double alpha, int64_t n, double* gam, double* b, double* a, double* c,
                              hipStream_t st);
-constexpr int kPlainChunkDD = 256;
-bool plain_dd_single_fits(int64_t N, int d, int tables);
-int plain_dd_max_local_chunks(int d);
-int plain_dd_part_doubles(int G);
-// single: the one-workgroup form; otherwise A.G cooperative workgroups (flags zero)
-hipError_t launch_plain_dd(const PlainArgs& A, bool single, int kind, hipStream_t st);
+size_t plain_dd_chain_lds(int d, bool per_comp, int64_t chunks, bool alone);
+int plain_dd_worker_chunks(int d);
+hipError_t launch_plain_dd(const PlainArgs& A, int kind, hipStream_t st);
 
 // ---- blocked method: groups and work items --------------------------------
 // A group is a set of trajectories sharing their orders (one weight table, or

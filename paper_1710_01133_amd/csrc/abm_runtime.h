@@ -101,9 +101,6 @@ struct abm_plan_s {
     // plain path (B == 1)
     bool plain_ok = false;
     abm::PlainShape plain{};
-    int plain_G = 0;              // double-double kernels' shape
-    int plain_nloc = 0;
-    bool plain_single = false;
     bool dd = false;              // double-double plan (ABM_FAR_DD): plain path only, tables
                                   // of (hi, lo) pairs
     std::string plain_error;
@@ -165,13 +162,13 @@ struct PlainTables {
     const double* gam[4];
     double alpha[4];
 };
+// (far_prec of p: double, or double-double)
 abm_status plain_shape(const abm_problem& p, int n_cu, PlainShape* out);
 PlainArgs plain_args(const abm_problem& prob, const PlainTables& T, const PlainShape& sh,
                      double* work, uint32_t* flags, uint32_t* status, double* y_out);
 // flags reset and the kernel, on st
-hipError_t plain_enqueue(const PlainArgs& A, const PlainShape& sh, int kind, hipStream_t st);
+hipError_t plain_enqueue(const PlainArgs& A, const PlainShape& sh, int kind, bool dd, hipStream_t st);
 abm_status plain_setup(abm_plan_s* pl);
-abm_status plain_setup_dd(abm_plan_s* pl);
 abm_status batch_setup(abm_plan_s* pl);
 void batch_teardown(abm_plan_s* pl);
 void free_reduced(WeightTable& t);

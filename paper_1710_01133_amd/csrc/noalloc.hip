@@ -149,7 +149,7 @@ extern "C" abm_status abm_solve_noalloc(const abm_problem* prob, double* y_out, 
     const PlainArgs A =
         plain_args(*prob, T, sh, reinterpret_cast<double*>(arr_dev.slots),
                    reinterpret_cast<uint32_t*>(base + kFlagsOff), status, y_out);
-    if ((e = plain_enqueue(A, sh, chain_kind(prob->rhs, orders_differ(*prob)), st)) != hipSuccess)
+    if ((e = plain_enqueue(A, sh, chain_kind(prob->rhs, orders_differ(*prob)), false, st)) != hipSuccess)
         return hip_fail(e, "plain kernel launch");
     return ABM_OK;
 }

@@ -24,9 +24,10 @@
 // What bounds it: the sequencer's instructions (one wave; an f64 operation
 // issues every 4.2 cycles whether or not it depends on the one before, and so
 // does every other instruction), 0.053 us per step for the linear equation,
-// 0.100 for the oscillator, 0.138 for Lorenz, at any length; one reduction per
-// step took 0.91 (8192 steps of the linear equation, one workgroup) and 2.9
-// (200000 steps of the oscillator).  Hence the 64 rows unrolled (a lane index
+// 0.100 for the oscillator, 0.138 for Lorenz, at any length (double-double:
+// 0.45, 1.00, 1.4); one reduction per step took 0.91 (8192 steps of the linear
+// equation, one workgroup) and 2.9 (200000 steps of the oscillator;
+// double-double 2.4 and 5.0).  Hence the 64 rows unrolled (a lane index
 // in an SGPR costs a readlane twice the time: 0.135 us per step of the
 // oscillator with a rolled loop) and the weights read one group of rows ahead.
 // Every sum is taken in an order fixed by (N, W) alone.  Short histories run
@@ -56,10 +57,12 @@ struct Num<double> {
     static constexpr int LR = 8;
     static constexpr bool kUnroll = true;    // the sequencer's 64 rows unrolled
     static __device__ __forceinline__ double zero() { return 0.0; }
-    static __device__ __forceinline__ double neg(double a) { return -a; }
-    // acc - w f: as a multiply-add of -f it takes acc from scalar registers
-    static __device__ __forceinline__ double mac_neg(double w, double f, double acc) { return fma(w, -f, acc); }
-    static __device__ __forceinline__ double mac(double w, double f, double acc) { return fma(w, f, acc); }
+    static __device__ __forceinline__ double mac(double w, double f, double acc) { return fma(w, f, acc); }   // acc + w f
+    static __device__ __forceinline__ double mul_add(double a, double b, double c) { return fma(a, b, c); }
+    // mac for a step's newest term, w = newest_weight(weight): as a
+    // multiply-add of -f it takes acc from scalar registers
+    static __device__ __forceinline__ double newest_weight(double w) { return -w; }
+    static __device__ __forceinline__ double newest(double w, double f, double acc) { return fma(w, -f, acc); }
     static __device__ __forceinline__ double add(double a, double b) { return a + b; }
     static __device__ __forceinline__ double mul(double a, double b) { return a * b; }
     static __device__ __forceinline__ double of(double x) { return x; }
@@ -76,6 +79,8 @@ struct Num<double> {
         return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
     }
     static __device__ __forceinline__ double swap(double v, int mask) { return __shfl_xor(v, mask, kWave); }
+    static __device__ __forceinline__ double get(const double* p) { return *as_global(p); }
+    static __device__ __forceinline__ void put(double* p, double v) { *as_global(p) = v; }
     static __device__ __forceinline__ double ld_agent(const double* p) { return ld_relaxed(p); }
     static __device__ __forceinline__ void st_agent(double* p, double v)
     {
@@ -128,7 +133,7 @@ struct alignas(16) Weight {
 };
 // one row of a chunk, or of the states
 template <class T, int D>
-struct alignas(D % 2 == 0 ? 16 : 8) Row {
+struct alignas(sizeof(T) * D % 16 == 0 ? 16 : 8) Row {
     T v[D];
 };
 
@@ -227,12 +232,12 @@ __device__ __forceinline__ void sum_chunks(const PlainArgs& A, int q, int c0, in
             for (int i = 0; i < D; ++i) acc[j][u][i] = Num<T>::zero();
     T nb[2], na[2];
     auto fetch = [&](int c, int w) {
-        const gptr<const T> tb = as_global((const T*)A.b[w]), ta = as_global((const T*)A.a[w]);
+        const T *tb = (const T*)A.b[w], *ta = (const T*)A.a[w];
         const int64_t at = (int64_t)kB * (q - c - 1) + lane;
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-            nb[e] = tb[at + kWave * e];
-            na[e] = ta[at + kWave * e];
+            nb[e] = Num<T>::get(tb + at + kWave * e);
+            na[e] = Num<T>::get(ta + at + kWave * e);
         }
     };
     auto stage = [&]() {
@@ -328,7 +333,7 @@ __device__ __forceinline__ void chain(const PlainArgs& A, T* sm, uint32_t* s_abo
                 T v = M::zero();
 #pragma unroll
                 for (int e = 0; e < D; ++e)
-                    if (e == i) v = M::mul(tab[n], F0[e]);
+                    if (e == i) v = M::mul(M::get(tab + n), F0[e]);
                 if (far) {
                     if (jj == 0) {
                         // the flags of the sources reach q once their slots hold block q
@@ -367,7 +372,7 @@ __device__ __forceinline__ void chain(const PlainArgs& A, T* sm, uint32_t* s_abo
             const int64_t w = out_index(s, A.N, A.out_stride);
             if (w >= 0) {
 #pragma unroll
-                for (int i = 0; i < D; ++i) as_global((T*)A.y_out)[w * D + i] = y[i];
+                for (int i = 0; i < D; ++i) M::put((T*)A.y_out + w * D + i, y[i]);
             }
         }
     };
@@ -380,22 +385,21 @@ __device__ __forceinline__ void chain(const PlainArgs& A, T* sm, uint32_t* s_abo
     };
 
     if (wave == 0) {
-        constexpr int GS = NW == 1 ? 4 : NW == 2 ? 2 : 1;
+        constexpr int GS = !M::kUnroll ? 1 : NW == 1 ? 4 : NW == 2 ? 2 : 1;
         __builtin_amdgcn_s_setprio(3);
         double p[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) p[i] = A.p[i];
-        // ha = h^alpha; its products with -b_0, -a_0 (the newest term) and
-        // with 1 / Gamma(alpha + 2)
-        T ha[D], hb[D], hc[D], hg[D], x1[D];
+        // h^alpha, and times 1 / Gamma(alpha + 2), b_0, a_0 (as newest takes them)
+        T ha[D], gi[D], b0[D], a0[D], x1[D];
         bool deriv = false;
 #pragma unroll
         for (int i = 0; i < D; ++i) {
             const int w = PC ? i : 0;
             ha[i] = M::power(A.h, A.alpha[w]);
-            hb[i] = M::neg(M::mul(ha[i], ((const T*)A.b[w])[0]));
-            hc[i] = M::neg(M::mul(ha[i], ((const T*)A.a[w])[0]));
-            hg[i] = M::mul(ha[i], M::recip(((const T*)A.gam[w])[1]));
+            gi[i] = M::mul(ha[i], M::recip(((const T*)A.gam[w])[1]));
+            b0[i] = M::newest_weight(M::mul(ha[i], ((const T*)A.b[w])[0]));
+            a0[i] = M::newest_weight(M::mul(ha[i], ((const T*)A.a[w])[0]));
             x1[i] = M::of(A.alpha[w] > 1.0 ? A.x1[i] : 0.0);
             deriv = deriv || A.alpha[w] > 1.0;
         }
@@ -416,21 +420,28 @@ __device__ __forceinline__ void chain(const PlainArgs& A, T* sm, uint32_t* s_abo
                 return;
             }
             const int rows = (int)(A.N - (int64_t)m * kB < kB ? A.N - (int64_t)m * kB : kB);
-#pragma unroll
-            for (int j = 0; j < 2 * D; ++j) {
-                P[j] = part_at(m, 0)[j * kB + lane];
-                for (int e = 1; e < np; ++e) P[j] = M::add(P[j], part_at(m, e)[j * kB + lane]);
-                P[j] = M::add(P[j], nxt[j]);
-                nxt[j] = M::zero();
-            }
             const T fr = frc[(m & 1) * kB + lane];
-            T base[D];                        // start term of this lane's row
+            // this lane's row: start term and h^alpha times the sums over the
+            // older chunks (base), which are large beside the sums over the
+            // newest two (P): kept apart, so that the 64 to 127 terms added
+            // one by one round at the size of P
+            T base[2 * D];
 #pragma unroll
             for (int i = 0; i < D; ++i) base[i] = x0[i];
             if (deriv) {
                 const T t = M::time((int64_t)m * kB + lane + 1, A.h);
 #pragma unroll
-                for (int i = 0; i < D; ++i) base[i] = M::mac(t, x1[i], x0[i]);
+                for (int i = 0; i < D; ++i) base[i] = M::mul_add(t, x1[i], x0[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < D; ++i) base[D + i] = base[i];
+#pragma unroll
+            for (int j = 0; j < 2 * D; ++j) {
+                T v = part_at(m, 0)[j * kB + lane];
+                for (int e = 1; e < np; ++e) v = M::add(v, part_at(m, e)[j * kB + lane]);
+                base[j] = M::mul_add(ha[j % D], v, base[j]);
+                P[j] = nxt[j];
+                nxt[j] = M::zero();
             }
             Row<T, D>* Fm = lane == 0 ? reinterpret_cast<Row<T, D>*>(chunk_at(m)) : spare;
             Row<T, D>* Ym = lane == 0 ? reinterpret_cast<Row<T, D>*>(Y + (m & 1) * kB * D) : spare;
@@ -465,24 +476,18 @@ __device__ __forceinline__ void chain(const PlainArgs& A, T* sm, uint32_t* s_abo
 #pragma unroll
                 for (int e = 0; e < GS; ++e) {
                     const int r = r0 + e;
-                    // row r's start term and sums but for the newest term
-                    T u[2 * D];
-#pragma unroll
-                    for (int i = 0; i < D; ++i) {
-                        u[i] = M::lane(M::mac(ha[i], P[i], base[i]), r);
-                        u[D + i] = M::lane(M::mac(ha[i], P[D + i], base[i]), r);
-                    }
-                    const T f_t = M::lane(fr, r);
+                    T yP[D], fP[D], C[D];
                     Row<T, D> y;
-                    T yP[D], fP[D];
+                    const T f_t = M::lane(fr, r);
+                    // lane r's value broadcast, the newest term added to it
 #pragma unroll
                     for (int i = 0; i < D; ++i) {
-                        yP[i] = M::mac_neg(hb[i], Fp.v[i], u[i]);
-                        u[D + i] = M::mac_neg(hc[i], Fp.v[i], u[D + i]);
+                        yP[i] = M::newest(b0[i], Fp.v[i], M::lane(M::mul_add(ha[i], P[i], base[i]), r));
+                        C[i] = M::newest(a0[i], Fp.v[i], M::lane(M::mul_add(ha[i], P[D + i], base[D + i]), r));
                     }
                     M::template rhs<R, D>(p, yP, f_t, fP);
 #pragma unroll
-                    for (int i = 0; i < D; ++i) y.v[i] = M::mac(hg[i], fP[i], u[D + i]);
+                    for (int i = 0; i < D; ++i) y.v[i] = M::mac(gi[i], fP[i], C[i]);
                     // the row before's f into the later rows (row l of this
                     // block: weight l - r, of the next one: 64 + l - r; rows
                     // already done receive what is never read)
