@@ -217,8 +217,11 @@ abm_status abm_solve(abm_plan_t *plan, const abm_problem *prob, double *y_out);
 /* B trajectories by the blocked method: history older than the current block
  * of L steps enters through a Toeplitz-weight x history product on the matrix
  * cores, the last steps through a near band kept on chip, and the sequential
- * predictor/corrector runs per trajectory in double.  y_out is a host array of
- * B device pointers, each sized as for abm_solve.  stats may be NULL.
+ * predictor/corrector runs per trajectory in double.  A single trajectory
+ * with the double far field that abm_solve accepts runs as abm_solve does
+ * (unless the plan is for column tiles only): stats then count one chain
+ * launch and no far-field work.  y_out is a host array of B device pointers,
+ * each sized as for abm_solve.  stats may be NULL.
  * Errors: ABM_EINVAL, ABM_EDEVICE. */
 abm_status abm_solve_batch(abm_plan_t *plan, const abm_problem *probs, int32_t B,
                            double *const *y_out, abm_stats *stats);

@@ -364,17 +364,7 @@ abm_status abm_solve(abm_plan_t* pl, const abm_problem* prob, double* y_out)
         return fail(ABM_EINVAL, "problem does not match the plan (rhs, d, orders, N, far_prec, out_stride)");
     hipError_t e = hipSetDevice(pl->ctx->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
-    PlainTables T{};
-    for (int i = 0; i < 4; ++i) {
-        const WeightTable& t = pl->tables[pl->table_of[i]];
-        T.b[i] = t.b;
-        T.a[i] = t.a;
-        T.c[i] = t.c;
-        T.gam[i] = t.gam;
-        T.alpha[i] = t.alpha;
-    }
-    const PlainArgs A = plain_args(*prob, T, pl->plain, pl->part, pl->flags, pl->status, y_out);
-    e = plain_enqueue(A, pl->plain, chain_kind(prob->rhs, orders_differ(*prob)), pl->dd, pl->ctx->stream);
+    e = plain_run(pl, *prob, y_out);
     if (e != hipSuccess) return hip_fail(e, "plain kernel launch");
     return ABM_OK;
 }
@@ -481,6 +471,21 @@ hipError_t plain_enqueue(const PlainArgs& A, const PlainShape& sh, int kind, boo
         if (e != hipSuccess) return e;
     }
     return dd ? launch_plain_dd(A, kind, st) : launch_plain(A, kind, st);
+}
+
+hipError_t plain_run(abm_plan_s* pl, const abm_problem& prob, double* y_out)
+{
+    PlainTables T{};
+    for (int i = 0; i < 4; ++i) {
+        const WeightTable& t = pl->tables[pl->table_of[i]];
+        T.b[i] = t.b;
+        T.a[i] = t.a;
+        T.c[i] = t.c;
+        T.gam[i] = t.gam;
+        T.alpha[i] = t.alpha;
+    }
+    const PlainArgs A = plain_args(prob, T, pl->plain, pl->part, pl->flags, pl->status, y_out);
+    return plain_enqueue(A, pl->plain, chain_kind(prob.rhs, orders_differ(prob)), pl->dd, pl->ctx->stream);
 }
 
 abm_status plain_setup(abm_plan_s* pl)

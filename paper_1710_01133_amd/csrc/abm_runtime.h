@@ -168,6 +168,8 @@ PlainArgs plain_args(const abm_problem& prob, const PlainTables& T, const PlainS
                      double* work, uint32_t* flags, uint32_t* status, double* y_out);
 // flags reset and the kernel, on st
 hipError_t plain_enqueue(const PlainArgs& A, const PlainShape& sh, int kind, bool dd, hipStream_t st);
+// the one trajectory of a plan with B = 1 (plain_ok) on the context's stream
+hipError_t plain_run(abm_plan_s* pl, const abm_problem& prob, double* y_out);
 abm_status plain_setup(abm_plan_s* pl);
 abm_status batch_setup(abm_plan_s* pl);
 void batch_teardown(abm_plan_s* pl);

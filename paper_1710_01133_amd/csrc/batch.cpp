@@ -725,6 +725,38 @@ extern "C" abm_status abm_solve_batch(abm_plan_t* pl, const abm_problem* probs, 
     for (const Group& g : pl->groups) S.narrow_groups += g.narrow ? 1 : 0;
     S.far_macs = pl->far_macs;
 
+    // One trajectory in double whose history fits the workgroups of abm_solve
+    // runs there: the blocked convolution of a lone narrow group takes two or
+    // three launches per 256 steps and its one chain wave shares the chip with
+    // them (N = 8192 linear 0.19 us per step, 10^6 steps of the oscillator
+    // 0.31; abm_solve 0.055 and 0.10).  A plan made for column tiles keeps them.
+    if (B == 1 && pl->plain_ok && pl->groups[0].narrow && pl->groups[0].prec == ABM_FAR_FP64) {
+        S.history_macs = (int64_t)probs[0].d * probs[0].N * (probs[0].N + 1) / 2;
+        S.chain_launches = 1;
+        hipEvent_t ev[2] = {nullptr, nullptr};
+        if (pl->timing) {
+            while (pl->events.size() < 2) {
+                hipEvent_t x;
+                if ((e = hipEventCreate(&x)) != hipSuccess) return hip_fail(e, "event pool");
+                pl->events.push_back(x);
+            }
+            ev[0] = pl->events[0];
+            ev[1] = pl->events[1];
+            if ((e = hipEventRecord(ev[0], st)) != hipSuccess) return hip_fail(e, "timing event");
+        }
+        if ((e = plain_run(pl, probs[0], y_out[0])) != hipSuccess) return hip_fail(e, "plain kernel launch");
+        if (pl->timing) {
+            float ms = 0.f;
+            if ((e = hipEventRecord(ev[1], st)) != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess ||
+                (e = hipEventElapsedTime(&ms, ev[0], ev[1])) != hipSuccess)
+                return hip_fail(e, "event time");
+            S.chain_ms = ms;
+        }
+        S.far_macs = 0;
+        if (stats) *stats = S;
+        return ABM_OK;
+    }
+
     // per-solve descriptors (x0, p, h, outputs) through the pinned staging copies
     for (auto& g : pl->groups) {
         if (g.traj_ev_live) {
