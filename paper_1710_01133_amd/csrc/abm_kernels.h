@@ -119,6 +119,7 @@ struct CompWeights {
     const float* a32;
     const uint16_t* bh[3]; // bf16 split terms (far_prec bf16x3 / bf16x6)
     const uint16_t* ah[3];
+    const double* fft;     // spectra of the weights by lag (far_fft.hip), or null
     double alpha;
 };
 
@@ -139,6 +140,8 @@ struct GroupDev {
     int64_t rows;          // history rows allocated
     double* accn;          // [member][2][d][L] sums carried into the next block
     double* part[2];       // far partials [split][col][2L], by block parity
+    double* spec;          // spectra of the history blocks [p][ldF][kFftStride] (complex), or null
+    double* fpart;         // sums of the transforms [superblock parity][block][ldF][2L]
     const TrajDesc* traj;  // members
     int32_t d;
     int32_t narrow;        // 1: few columns, far field by the blocked convolution,
@@ -167,6 +170,18 @@ struct FarItem {
     int64_t ldP;           // column stride of the partial slices (active columns,
                            // padded to the tile width except in narrow groups;
                            // all columns of a per-component group)
+    int64_t k0;            // double column tiles: history 1 .. k0 is left to the transforms
+    int32_t kc;            // chunk rows of this item (0: the launch's)
+    int32_t pad_;
+};
+
+// Transforms of one group (or component) for superblock Q.
+struct FftItem {
+    int32_t group;
+    int32_t comp;          // weight tables: the group's w[comp]
+    int32_t coff;          // first history column
+    int32_t ncols;
+    int32_t Q;
 };
 
 // Chain of one trajectory (group member) through block m.
@@ -175,6 +190,8 @@ struct ChainItem {
     int32_t member;
     int32_t nsplit;        // far partial slices of this block (0 when m < 2)
     int32_t kind;          // chain_kind of the group
+    int32_t fslice;        // 1 + slice of the group's fpart that holds this block's sums; 0: none
+    int32_t pad_;
     int64_t mL;
     int64_t ldP;
 };
@@ -225,6 +242,18 @@ int hankel_chunk_rows();
 int hankel_split_plan(int64_t kfar, int L, int max_split, int* nchunks, int* chunks_per_split);
 int hankel_split_bound(int64_t kfar_max, int L, int max_split);
 size_t hankel_lds_bytes(int L, int max_tiles, int prec);
+// Old history by transforms (double, column tiles): rows of a superblock and
+// of a history block, complex values per stored half spectrum, chunk rows of
+// the direct products left beside it.
+constexpr int kFftRows = 2048;
+constexpr int kFftStride = kFftRows + 8;
+constexpr int kFftChunk = 256;
+hipError_t launch_fft_twiddles(double* tw, hipStream_t st);      // 2 kFftRows complex values
+// lags spectra of b and a (n entries each) for block length L
+hipError_t launch_fft_weights(const double* b, const double* a, int64_t n, int L, int lags, const double* tw,
+                              double* out, hipStream_t st);
+hipError_t launch_far_fft(const GroupDev* groups, const FftItem* items, int n, int max_cols, int L,
+                          const double* tw, hipStream_t st);
 // Sums the partial slices of each narrow far item into its first slice (in
 // slice order); the chain items of those blocks then read one slice.
 hipError_t launch_far_reduce(const GroupDev* groups, const FarItem* items, int n, int max_cols,

@@ -31,6 +31,7 @@ struct WeightTable {
     float* a32;
     uint16_t* bh[3];  // bf16 split terms of b
     uint16_t* ah[3];
+    double* fft;      // spectra of the weights by lag (on demand)
 };
 
 // Trajectories sharing their orders (one weight table per component, all the
@@ -65,6 +66,10 @@ struct Group {
     double* part[2] = {nullptr, nullptr};   // far partials by block parity
     size_t part_half = 0;           // doubles per partial buffer
     int nsplit_cap = 0;             // partial slices each buffer holds
+    bool fft = false;               // double column tiles of a batch: history before the
+                                    // superblock by transforms
+    double* spec = nullptr;
+    double* fpart = nullptr;
     TrajDesc* traj_host = nullptr;  // pinned staging copy of the descriptors
     hipEvent_t traj_ev = nullptr;   // recorded after the last upload from traj_host
     bool traj_ev_live = false;
@@ -111,14 +116,18 @@ struct abm_plan_s {
     bool allow_narrow = true;
     int L = 0;
     int kchunk = 0;
+    int kchunk64 = 0;             // chunk rows of the double column tiles
     int max_split = 8;
     std::vector<abm::Group> groups;
     abm::GroupDev* groups_dev = nullptr;
     abm::FarItem* far_items_dev = nullptr;
+    abm::FftItem* fft_items_dev = nullptr;
+    double* fft_tw = nullptr;     // twiddle factors
     abm::ChainItem* chain_items_dev = nullptr;
     abm::ChainItem* init_items_dev = nullptr;
     int64_t ticks = 0;
     std::vector<abm::Span> far_spans;     // [tick][far launch class]
+    std::vector<abm::Span> fft_spans;     // [tick] transforms of the block after the tick's
     std::vector<abm::Span> chain_spans;   // [tick][chain kind]
     std::vector<char> chain_spread;       // [tick]: chains one wave per SIMD (small far field beside)
     std::vector<abm::Span> init_spans;    // [rhs]

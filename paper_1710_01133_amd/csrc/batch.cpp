@@ -42,6 +42,8 @@ void free_reduced(WeightTable& t)
         t.bh[i] = t.ah[i] = nullptr;
     }
     t.b32 = t.a32 = nullptr;
+    dev_free(t.fft);
+    t.fft = nullptr;
 }
 
 void free_group(Group& g)
@@ -55,6 +57,8 @@ void free_group(Group& g)
     dev_free(g.traj_dev);
     dev_free(g.accn);
     dev_free(g.part[0]);
+    dev_free(g.spec);
+    dev_free(g.fpart);
     if (g.traj_host) (void)hipHostFree(g.traj_host);
     if (g.traj_ev) (void)hipEventDestroy(g.traj_ev);
     g = Group{};
@@ -74,6 +78,10 @@ void batch_teardown(abm_plan_s* pl)
     pl->groups.clear();
     dev_free(pl->groups_dev);
     dev_free(pl->far_items_dev);
+    dev_free(pl->fft_items_dev);
+    dev_free(pl->fft_tw);
+    pl->fft_items_dev = nullptr;
+    pl->fft_tw = nullptr;
     dev_free(pl->chain_items_dev);
     dev_free(pl->init_items_dev);
     pl->groups_dev = nullptr;
@@ -178,6 +186,7 @@ GroupDev group_dev(const Group& g, const WeightTable* const W[4])
             w.ah[i] = W[c]->ah[i];
         }
         w.alpha = W[c]->alpha;
+        w.fft = W[c]->fft;
     }
     for (int i = 0; i < 3; ++i) d.Fh[i] = g.Fh[i];
     d.Fsc = g.Fsc;
@@ -190,6 +199,8 @@ GroupDev group_dev(const Group& g, const WeightTable* const W[4])
     d.accn = g.accn;
     d.part[0] = g.part[0];
     d.part[1] = g.part[1];
+    d.spec = g.spec;
+    d.fpart = g.fpart;
     d.traj = g.traj_dev;
     d.d = g.d;
     d.narrow = g.narrow ? 1 : 0;
@@ -218,6 +229,14 @@ void group_layout(Group& g, int L)
     }
 }
 
+// Last history row that the direct far field of the block starting at row mL
+// leaves to the transforms.
+static int64_t direct_from(const Group& g, int64_t mL, int L)
+{
+    const int64_t Q = mL / kFftRows;
+    return g.fft && Q > 0 ? Q * kFftRows - L : 0;
+}
+
 // Work items of group g (index gi) when it is at block m: the far field of
 // block m+1 and the chains of block m.  memberN holds the members' N in the
 // group's (descending) order, so the members still running form a prefix.
@@ -234,12 +253,14 @@ void block_items(const Group& g, int gi, int64_t m, int L, int kchunk, int max_s
         return cnt;
     };
     const int64_t mf = m + 1;
-    if (far && mf < nblocks && mf >= 2) {
+    if (far && mf < nblocks && mf >= 2 && (mf - 1) * L > direct_from(g, mf * L, L)) {
         FarItem it{};
         it.group = gi;
         it.kfar = (mf - 1) * L;
         it.mL = mf * L;
-        it.nsplit = group_split_plan(g, it.kfar, L, kchunk, max_split, &it.nchunks,
+        it.k0 = direct_from(g, mf * L, L);
+        it.kc = g.fft ? kFftChunk : 0;
+        it.nsplit = group_split_plan(g, it.kfar - it.k0, L, kchunk, max_split, &it.nchunks,
                                      &it.chunks_per_split);
         const int64_t na = active(mf);
         if (g.per_comp) {
@@ -267,7 +288,9 @@ void block_items(const Group& g, int gi, int64_t m, int L, int kchunk, int max_s
     }
     if (chain && m < nblocks) {
         int nsp = 0, nc = 0, cps = 0;
-        if (m >= 2) nsp = group_split_plan(g, (m - 1) * L, L, kchunk, max_split, &nc, &cps);
+        const int64_t k0 = direct_from(g, m * L, L);
+        if (m >= 2 && (m - 1) * L > k0)
+            nsp = group_split_plan(g, (m - 1) * L - k0, L, kchunk, max_split, &nc, &cps);
         const int32_t na = active(m);
         const int64_t ldP = g.per_comp ? g.ldF
                           : g.narrow  ? (int64_t)na * g.d
@@ -278,6 +301,9 @@ void block_items(const Group& g, int gi, int64_t m, int L, int kchunk, int max_s
             c.member = j;
             c.kind = chain_kind(g.rhs, g.per_comp);
             c.nsplit = nsp;
+            const int64_t Q = m * L / kFftRows;
+            if (g.fft && Q > 0)
+                c.fslice = (int32_t)(1 + (Q & 1) * (kFftRows / L) + (m * L - Q * kFftRows) / L);
             c.mL = m * L;
             c.ldP = ldP;
             chain->push_back(c);
@@ -291,7 +317,7 @@ int group_split_plan(const Group& g, int64_t kfar, int L, int kchunk, int max_sp
     if (g.narrow)
         return hankel_split_plan(kfar, L, g.split_cap > 0 ? g.split_cap : max_split, nchunks,
                                  chunks_per_split);
-    return far_split_plan(kfar, kchunk, max_split, nchunks, chunks_per_split);
+    return far_split_plan(kfar, g.fft ? kFftChunk : kchunk, max_split, nchunks, chunks_per_split);
 }
 
 int64_t group_far_split_max(const Group& g, int L, int kchunk, int max_split)
@@ -299,6 +325,7 @@ int64_t group_far_split_max(const Group& g, int L, int kchunk, int max_split)
     const int64_t nblocks = (g.nmax + L - 1) / L;
     const int64_t kfar_max = nblocks >= 2 ? (nblocks - 2) * L : 0;   // far(m) covers (m-1)L
     if (g.narrow) return hankel_split_bound(kfar_max, L, g.split_cap > 0 ? g.split_cap : max_split);
+    if (g.fft) return far_split_bound(std::min<int64_t>(kfar_max, kFftRows), kFftChunk, max_split);
     return far_split_bound(kfar_max, kchunk, max_split);
 }
 
@@ -326,6 +353,44 @@ abm_status choose_blocking(abm_plan_s* pl, const abm_problem* probs, int B)
         return fail(ABM_EINVAL, "split count %d out of range 1..4096", pl->max_split);
     pl->allow_narrow = !T.column_tiles_only && env_int("ABM_NARROW", 1) != 0;
     return ABM_OK;
+}
+
+// Spectra of group g's history and of its weights, if it reaches a second
+// superblock.  Where the device has no room for them the group keeps the
+// direct products over its whole history.
+static abm_status setup_transforms(abm_plan_s* pl, Group& g, hipStream_t st)
+{
+    const int lags = (int)((g.nmax - 1) / kFftRows);
+    if (lags < 1) return ABM_OK;
+    const size_t spec = (size_t)lags * g.ldF * kFftStride * 2 * sizeof(double);
+    const size_t sums = (size_t)4 * kFftRows * g.ldF * sizeof(double);
+    abm_status s = ABM_OK;
+    hipError_t e = hipSuccess;
+    if (!pl->fft_tw) {
+        s = dev_alloc((void**)&pl->fft_tw, (size_t)4 * kFftRows * sizeof(double), "twiddle factors");
+        if (s == ABM_OK && (e = launch_fft_twiddles(pl->fft_tw, st)) != hipSuccess)
+            return hip_fail(e, "twiddle kernel");
+    }
+    if (s == ABM_OK) s = dev_alloc((void**)&g.spec, spec, "history spectra");
+    if (s == ABM_OK) s = dev_alloc((void**)&g.fpart, sums, "transform sums");
+    for (int c = 0; c < (g.per_comp ? g.d : 1) && s == ABM_OK; ++c) {
+        WeightTable& t = pl->tables[g.table[c]];
+        if (t.fft) continue;
+        const int all = (int)((t.n - 1) / kFftRows);   // for the table's longest user
+        s = dev_alloc((void**)&t.fft, (size_t)all * 2 * kFftStride * 2 * sizeof(double), "weight spectra");
+        if (s == ABM_OK && (e = launch_fft_weights(t.b, t.a, t.n + kWeightPad, pl->L, all, pl->fft_tw, t.fft,
+                                                   st)) != hipSuccess)
+            return hip_fail(e, "weight spectra");
+    }
+    if (s == ABM_ENOMEM) {
+        (void)hipGetLastError();
+        dev_free(g.spec);
+        dev_free(g.fpart);
+        g.spec = g.fpart = nullptr;
+        g.fft = false;
+        return ABM_OK;
+    }
+    return s;
 }
 
 abm_status batch_setup(abm_plan_s* pl)
@@ -382,9 +447,15 @@ abm_status batch_setup(abm_plan_s* pl)
             if ((s = ensure_reduced_weights(pl->tables[g.table[c]], g.prec, st))) return s;
             W[c] = &pl->tables[g.table[c]];
         }
+        g.fft = !g.narrow && g.prec == ABM_FAR_FP64;
+        if (g.fft && (s = setup_transforms(pl, g, st))) return s;
         if ((s = alloc_group(g, L, (int)group_far_split_max(g, L, kchunk, pl->max_split), st))) return s;
         gdev.push_back(group_dev(g, W));
     }
+
+    pl->kchunk64 = kFftChunk;
+    for (const Group& g : pl->groups)
+        if (!g.narrow && g.prec == ABM_FAR_FP64 && !g.fft) pl->kchunk64 = kchunk;
 
     // static tick schedule: far items by precision class, chain items by rhs
     const int ngroups = (int)pl->groups.size();
@@ -395,8 +466,31 @@ abm_status batch_setup(abm_plan_s* pl)
     pl->far_spans.assign((size_t)ticks * kFarClasses, Span{});
     pl->chain_spans.assign((size_t)ticks * kChainKinds, Span{});
     std::vector<FarItem> far_all;
+    std::vector<FftItem> fft_all;
+    pl->fft_spans.assign((size_t)ticks, Span{});
     std::vector<ChainItem> chain_all, init_all;
     for (int64_t t = 0; t < ticks; ++t) {
+        // the block after the tick's starts superblock Q: its transforms
+        Span& fs = pl->fft_spans[t];
+        fs.offset = (int64_t)fft_all.size();
+        const int64_t Q = (t + 1) * L / kFftRows;
+        for (int gi = 0; gi < ngroups && (t + 1) * L % kFftRows == 0; ++gi) {
+            const Group& g = pl->groups[gi];
+            if (!g.fft || g.nmax <= Q * kFftRows) continue;
+            int32_t na = 0;
+            for (int64_t N : memberN[gi]) na += N > Q * kFftRows ? 1 : 0;
+            for (int c = 0; c < (g.per_comp ? g.d : 1); ++c) {
+                FftItem it{};
+                it.group = gi;
+                it.comp = c;
+                it.coff = (int32_t)(g.per_comp ? c * g.ldC : 0);
+                it.ncols = g.per_comp ? na : na * g.d;
+                it.Q = (int32_t)Q;
+                fft_all.push_back(it);
+                fs.max_cols = std::max(fs.max_cols, it.ncols);
+            }
+        }
+        fs.count = (int32_t)((int64_t)fft_all.size() - fs.offset);
         for (int cls = 0; cls < kFarClasses; ++cls) {
             Span& sp = pl->far_spans[t * kFarClasses + cls];
             sp.offset = (int64_t)far_all.size();
@@ -460,11 +554,13 @@ abm_status batch_setup(abm_plan_s* pl)
     hipError_t e;
     if ((s = dev_alloc((void**)&pl->groups_dev, gdev.size() * sizeof(GroupDev), "group table")) ||
         (s = dev_alloc((void**)&pl->far_items_dev, std::max<size_t>(1, far_all.size()) * sizeof(FarItem), "far items")) ||
+        (s = dev_alloc((void**)&pl->fft_items_dev, std::max<size_t>(1, fft_all.size()) * sizeof(FftItem), "transform items")) ||
         (s = dev_alloc((void**)&pl->chain_items_dev, std::max<size_t>(1, chain_all.size()) * sizeof(ChainItem), "chain items")) ||
         (s = dev_alloc((void**)&pl->init_items_dev, std::max<size_t>(1, init_all.size()) * sizeof(ChainItem), "init items")))
         return s;
     if ((e = hipMemcpy(pl->groups_dev, gdev.data(), gdev.size() * sizeof(GroupDev), hipMemcpyHostToDevice)) ||
         (!far_all.empty() && (e = hipMemcpy(pl->far_items_dev, far_all.data(), far_all.size() * sizeof(FarItem), hipMemcpyHostToDevice))) ||
+        (!fft_all.empty() && (e = hipMemcpy(pl->fft_items_dev, fft_all.data(), fft_all.size() * sizeof(FftItem), hipMemcpyHostToDevice))) ||
         (e = hipMemcpy(pl->chain_items_dev, chain_all.data(), chain_all.size() * sizeof(ChainItem), hipMemcpyHostToDevice)) ||
         (e = hipMemcpy(pl->init_items_dev, init_all.data(), init_all.size() * sizeof(ChainItem), hipMemcpyHostToDevice)))
         return hip_fail(e, "schedule upload");
@@ -479,7 +575,7 @@ abm_status batch_setup(abm_plan_s* pl)
                 const Group& g = pl->groups[it.group];
                 for (int64_t N : memberN[it.group]) {
                     if (N <= it.mL) continue;
-                    tick_macs[t] += (int64_t)(g.per_comp ? 1 : g.d) * std::min<int64_t>(L, N - it.mL) * it.kfar;
+                    tick_macs[t] += (int64_t)(g.per_comp ? 1 : g.d) * std::min<int64_t>(L, N - it.mL) * (it.kfar - it.k0);
                 }
             }
         }
@@ -586,16 +682,27 @@ struct TickEnqueuer {
             bool any_far = false;
             for (int cls = 0; cls < kFarClasses; ++cls)
                 if (pl->far_spans[t * kFarClasses + cls].count) any_far = true;
+            const Span& fs = pl->fft_spans[t];
+            any_far = any_far || fs.count;
             hipEvent_t ev_far = nullptr;
             if (any_far) {
                 if (!alt && ev_chain_prev && (e = hipStreamWaitEvent(sf, ev_chain_prev, 0)) != hipSuccess)
                     return hip_fail(e, "stream wait");
+                if (fs.count) {
+                    e = timed(0, sf, [&]() {
+                        return launch_far_fft(pl->groups_dev, pl->fft_items_dev + fs.offset, fs.count,
+                                              fs.max_cols, L, pl->fft_tw, sf);
+                    });
+                    if (e != hipSuccess) return hip_fail(e, "transform launch");
+                    far_launches += 2;
+                }
                 for (int cls = 0; cls < kFarClasses; ++cls) {
                     const Span& sp = pl->far_spans[t * kFarClasses + cls];
                     if (!sp.count) continue;
                     e = timed(0, sf, [&]() {
+                        const int kc = cls == ABM_FAR_FP64 ? pl->kchunk64 : pl->kchunk;
                         return launch_far(pl->groups_dev, pl->far_items_dev + sp.offset, sp.count,
-                                          sp.max_x, sp.max_y, pl->kchunk, L, cls, sf);
+                                          sp.max_x, sp.max_y, kc, L, cls, sf);
                     });
                     if (e != hipSuccess) return hip_fail(e, "far-field launch");
                     ++far_launches;

@@ -8,7 +8,9 @@
 //   FF[L + r] = sum_{k=1..K} a_{mL+r-k} F_k          (corrector rows)
 // with F_k the time-major history row (all columns = trajectory components).
 // The k = 0 terms (b_n f_0, c_n f_0) and the near band are added by the chain
-// kernel.
+// kernel.  In a batch the products start at k = k0 + 1, the history since the
+// block's superblock began (far_fft.hip takes the older one), in chunks of
+// 256 rows.
 //
 // Tiling: one workgroup computes all 2L rows for 16*NT columns over a fixed
 // range of history chunks [k_lo, k_hi) (chunk boundaries and their grouping
@@ -37,6 +39,7 @@ __global__ __launch_bounds__(256) void k_far_f64(const GroupDev* groups, const F
     constexpr int TN = 16 * NT;      // columns per workgroup
     FarArgs A;
     if (!far_view(groups, items, kchunk, L, A)) return;
+    if (const int kc = items[blockIdx.z].kc) A.kchunk = kc;
     extern __shared__ double sm[];
     const int win = L + A.kchunk;    // weight window length (padded)
     double* wb = sm;                 // b window
@@ -87,7 +90,7 @@ __global__ __launch_bounds__(256) void k_far_f64(const GroupDev* groups, const F
     int c_end = c_begin + A.chunks_per_split;
     if (c_end > A.nchunks) c_end = A.nchunks;
     for (int chunk = c_begin; chunk < c_end; ++chunk) {
-        const int64_t k_lo = 1 + (int64_t)chunk * A.kchunk;
+        const int64_t k_lo = A.k0 + 1 + (int64_t)chunk * A.kchunk;
         int64_t k_hi = k_lo + A.kchunk;
         if (k_hi > A.kfar + 1) k_hi = A.kfar + 1;
         const int nk = (int)(k_hi - k_lo);                    // multiple of kKS

@@ -20,6 +20,7 @@ struct FarArgs {
     int64_t rows;
     int64_t mL;
     int64_t kfar;
+    int64_t k0;
     int32_t kchunk;
     int32_t nchunks;
     int32_t chunks_per_split;
@@ -83,6 +84,7 @@ __device__ __forceinline__ bool far_view_at(const GroupDev* __restrict__ groups,
     A.rows = G.rows;
     A.mL = it.mL;
     A.kfar = it.kfar;
+    A.k0 = it.k0;
     A.kchunk = kchunk;
     A.nchunks = it.nchunks;
     A.chunks_per_split = it.chunks_per_split;
