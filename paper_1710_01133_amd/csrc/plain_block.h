@@ -46,6 +46,36 @@
 
 namespace abm {
 
+// Of each pair of lanes l, l ^ mask the upper one's a and the lower one's b
+// change places (mask 32, 16 or 8): vector moves, where a shuffle goes through
+// the LDS unit twice per double.
+__device__ __forceinline__ void exchange_halves(uint32_t& a, uint32_t& b, int mask)
+{
+    if (mask == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+        a = r[0];
+        b = r[1];
+    } else if (mask == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+        a = r[0];
+        b = r[1];
+    } else {
+        // rows of 16 lanes rotated by 8, into their upper (banks 2, 3) and lower half
+        const uint32_t up = (uint32_t)__builtin_amdgcn_update_dpp((int)a, (int)b, 0x128, 0xf, 0xc, false);
+        b = (uint32_t)__builtin_amdgcn_update_dpp((int)b, (int)a, 0x128, 0xf, 0x3, false);
+        a = up;
+    }
+}
+__device__ __forceinline__ void exchange_halves(double& a, double& b, int mask)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, a), v = __builtin_bit_cast(uint64_t, b);
+    uint32_t al = (uint32_t)u, ah = (uint32_t)(u >> 32), bl = (uint32_t)v, bh = (uint32_t)(v >> 32);
+    exchange_halves(al, bl, mask);
+    exchange_halves(ah, bh, mask);
+    a = __builtin_bit_cast(double, ((uint64_t)ah << 32) | al);
+    b = __builtin_bit_cast(double, ((uint64_t)bh << 32) | bl);
+}
+
 // Arithmetic of the path in the type T (double here; double-double in
 // plain_dd.hip).  LR: lanes along the rows in a chunk product (64 / LR rows
 // per lane: as many as the registers hold).
@@ -79,6 +109,7 @@ struct Num<double> {
         return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
     }
     static __device__ __forceinline__ double swap(double v, int mask) { return __shfl_xor(v, mask, kWave); }
+    static __device__ __forceinline__ void exchange(double& a, double& b, int mask) { exchange_halves(a, b, mask); }
     static __device__ __forceinline__ double get(const double* p) { return *as_global(p); }
     static __device__ __forceinline__ void put(double* p, double v) { *as_global(p) = v; }
     static __device__ __forceinline__ double ld_agent(const double* p) { return ld_relaxed(p); }
@@ -190,23 +221,36 @@ __device__ __forceinline__ void chunk_mac(const Weight<T>* win, const T* Fc, int
     }
 }
 
-// Sums of the lane groups: lane l ends with row l's sums in out.
+// Sums of the lane groups: lane l ends with row l's sums in out.  Every wave
+// of a block pays this once per target block; exchanging lanes with vector
+// moves instead of shuffles (two trips through the LDS unit per double, and
+// four selects) took the linear system of 8192 steps from 536 to 528 us, the
+// oscillator of 200000 from 20.1 to 19.8 ms and of 10^6 from 145.9 to 140.0;
+// in double-double 3.91 to 3.48 ms for one component.  Two components there
+// measured slower with the moves (100000 steps 100.0 against 112.6 ms: the
+// rolled loop of the sequencer is scheduled worse around them), so they shuffle.
 template <class T, int D>
 __device__ __forceinline__ void group_sum(T (&acc)[kB / Num<T>::LR][2][D], int lane, T* out)
 {
+    using M = Num<T>;
     constexpr int RP = kB / Num<T>::LR;
 #pragma unroll
     for (int half = RP / 2, mask = 32; half >= 1; half >>= 1, mask >>= 1) {
-        const bool up = (lane & mask) != 0;
 #pragma unroll
         for (int j = 0; j < half; ++j)
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
                 for (int i = 0; i < D; ++i) {
-                    const T keep = up ? acc[j + half][u][i] : acc[j][u][i];
-                    const T give = up ? acc[j][u][i] : acc[j + half][u][i];
-                    acc[j][u][i] = Num<T>::add(keep, Num<T>::swap(give, mask));
+                    if constexpr (M::kUnroll || D == 1) {
+                        M::exchange(acc[j][u][i], acc[j + half][u][i], mask);
+                        acc[j][u][i] = M::add(acc[j][u][i], acc[j + half][u][i]);
+                    } else {
+                        const bool up = (lane & mask) != 0;
+                        const T keep = up ? acc[j + half][u][i] : acc[j][u][i];
+                        const T give = up ? acc[j][u][i] : acc[j + half][u][i];
+                        acc[j][u][i] = M::add(keep, M::swap(give, mask));
+                    }
                 }
     }
 #pragma unroll

@@ -224,6 +224,11 @@ struct Num<dd> {
     static __device__ __forceinline__ dd nan() { return dd{__builtin_nan(""), __builtin_nan("")}; }
     static __device__ __forceinline__ dd lane(dd v, int l) { return dd{Num<double>::lane(v.hi, l), Num<double>::lane(v.lo, l)}; }
     static __device__ __forceinline__ dd swap(dd v, int mask) { return dd{Num<double>::swap(v.hi, mask), Num<double>::swap(v.lo, mask)}; }
+    static __device__ __forceinline__ void exchange(dd& a, dd& b, int mask)
+    {
+        exchange_halves(a.hi, b.hi, mask);
+        exchange_halves(a.lo, b.lo, mask);
+    }
     static __device__ __forceinline__ dd get(const dd* p) { return dd{*as_global(&p->hi), *as_global(&p->lo)}; }
     static __device__ __forceinline__ void put(dd* p, dd v)
     {
