@@ -7,7 +7,7 @@ matrix cores, near band and predictor/corrector chain, outputs every 1024th
 state.  Inputs are synthetic and already in HBM when the timed region starts.
 
 Printed: one JSON line with history MACs/s (d*N(N+1)/2 per trajectory) of the
-batched path, the plain per-step path on the single 200000-step oscillator
+batched path, the plain path on the single 200000-step oscillator
 for comparison, the far-field kernel's roofline position (live HIP-event
 timing of its launches), the error against the double oracle, and the oracle
 itself timed on the host cores on a bounded sample of the same sweep.
@@ -261,7 +261,7 @@ def cpu_baseline(inputs, budget_s=20.0):
 
 
 def plain_leg(abm, torch, inputs, ctx):
-    """The plain per-step path (abm_solve) on the single 200000-step oscillator."""
+    """The plain path (abm_solve) on the single 200000-step oscillator."""
     p1 = inputs.duffing_single()
     pp = abm.Plan(ctx, [p1], out_stride=0)
     y1 = abm.alloc_out(p1, 0)
@@ -286,7 +286,7 @@ def plain_leg(abm, torch, inputs, ctx):
            "us_per_step": dt1 / p1.N * 1e6,
            "streamed_bytes": algo_bytes, "effective_GBps": algo_bytes / dt1 / 1e9,
            "frac_of_hbm_peak": algo_bytes / dt1 / 8e12,
-           "note": "the history lives in LDS, so the bound is the per-step grid synchronisation"}
+           "note": "the history lives in LDS, so the bound is one wave's chain of dependent steps"}
     # the scalar linear test (D^0.8 y = -y, N = 8192): plain path and the
     # blocked path on the same single trajectory (a narrow group)
     p0 = inputs.linear_c()
@@ -422,7 +422,7 @@ def main():
                     help="only run a 1 GiB device copy (counter calibration)")
     ap.add_argument("--no-plain", action="store_true")
     ap.add_argument("--plain-only", action="store_true",
-                    help="only the plain per-step path on the 200000-step oscillator")
+                    help="only the plain path on the 200000-step oscillator")
     ap.add_argument("--serve-requests", type=int, default=2000,
                     help="requests of the serving stream (0 skips the serving leg)")
     ap.add_argument("--serve-arena-mib", type=int, nargs="+", default=[96, 8192],
