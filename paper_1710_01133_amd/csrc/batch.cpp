@@ -836,7 +836,7 @@ extern "C" abm_status abm_solve_batch(abm_plan_t* pl, const abm_problem* probs, 
     // runs there: the blocked convolution of a lone narrow group takes two or
     // three launches per 256 steps and its one chain wave shares the chip with
     // them (N = 8192 linear 0.19 us per step, 10^6 steps of the oscillator
-    // 0.31; abm_solve 0.055 and 0.10).  A plan made for column tiles keeps them.
+    // 0.31; abm_solve 0.065 and 0.14).  A plan made for column tiles keeps them.
     if (B == 1 && pl->plain_ok && pl->groups[0].narrow && pl->groups[0].prec == ABM_FAR_FP64) {
         S.history_macs = (int64_t)probs[0].d * probs[0].N * (probs[0].N + 1) / 2;
         S.chain_launches = 1;
