@@ -171,7 +171,13 @@ void abm_ctx_destroy(abm_ctx *ctx);
  * may change x0, x1, p and h.  Components of equal order share one weight
  * table.  Trajectories whose components have different orders are grouped
  * by their order tuple; their far field runs once per component with that
- * component's table. 
+ * component's table.
+ * Memory: a history takes 8 bytes per step and component, rounded up to its
+ * tiles.  Groups with a double far field in column tiles also keep spectra of
+ * their history, about twice its bytes.  Where the device has no room for all
+ * spectra of a plan, the plan is made without them and sums its whole history
+ * directly: slower for more than 2048 steps, and different by rounding from
+ * the same plan with them.
  * Errors: ABM_EINVAL (any invalid problem; the message names its index),
  * ABM_ENOMEM, ABM_EDEVICE. */
 abm_status abm_plan(abm_ctx *ctx, const abm_problem *probs, int32_t B, abm_plan_t **out);

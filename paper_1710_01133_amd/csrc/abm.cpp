@@ -126,15 +126,25 @@ int env_int(const char* name, int dflt)
     return atoi(v);
 }
 
+// Device bytes the plan being made on this thread may still allocate: no
+// bound, unless the ABM_PLAN_MEM_MIB test hook sets one (allocations beyond it
+// fail as the device's own would).
+static thread_local int64_t t_alloc_left = INT64_MAX;
+
+int64_t alloc_left() { return t_alloc_left; }
+void set_alloc_left(int64_t bytes) { t_alloc_left = bytes; }
+
 abm_status dev_alloc(void** p, size_t bytes, const char* what)
 {
     *p = nullptr;
     if (bytes == 0) return ABM_OK;
+    if (t_alloc_left != INT64_MAX && (int64_t)bytes > t_alloc_left) return hip_fail(hipErrorOutOfMemory, what);
     hipError_t e = hipMalloc(p, bytes);
     if (e != hipSuccess) {
         *p = nullptr;
         return hip_fail(e, what);
     }
+    if (t_alloc_left != INT64_MAX) t_alloc_left -= (int64_t)bytes;
     return ABM_OK;
 }
 
@@ -245,6 +255,8 @@ abm_status abm_plan_tuned(abm_ctx* ctx, const abm_problem* probs, int32_t B,
     pl->shape.assign(probs, probs + B);
     if (tune) pl->tune = *tune;
     abm_status st = ABM_OK;
+    const int mem_mib = env_int("ABM_PLAN_MEM_MIB", 0);
+    set_alloc_left(mem_mib > 0 ? (int64_t)mem_mib << 20 : INT64_MAX);
 
     // one weight table per distinct order, long enough for its longest user
     pl->table_of.assign((size_t)B * 4, 0);
@@ -297,6 +309,7 @@ abm_status abm_plan_tuned(abm_ctx* ctx, const abm_problem* probs, int32_t B,
         if (ps != ABM_OK) pl->plain_error = abm_last_error();
     }
     if (st == ABM_OK && !dd) st = batch_setup(pl);
+    set_alloc_left(INT64_MAX);
     if (st != ABM_OK) {
         abm_plan_destroy(pl);
         return st;

@@ -162,6 +162,9 @@ bool same_orders(const abm_problem& a, const abm_problem& b);
 int env_int(const char* name, int dflt);
 abm_status dev_alloc(void** p, size_t bytes, const char* what);
 void dev_free(void* p);
+// bound on the device bytes allocated for the plan this thread is making
+int64_t alloc_left();
+void set_alloc_left(int64_t bytes);
 
 // Weight tables of each component (all the same unless orders differ).
 struct PlainTables {

@@ -356,8 +356,7 @@ abm_status choose_blocking(abm_plan_s* pl, const abm_problem* probs, int B)
 }
 
 // Spectra of group g's history and of its weights, if it reaches a second
-// superblock.  Where the device has no room for them the group keeps the
-// direct products over its whole history.
+// superblock.
 static abm_status setup_transforms(abm_plan_s* pl, Group& g, hipStream_t st)
 {
     const int lags = (int)((g.nmax - 1) / kFftRows);
@@ -382,18 +381,12 @@ static abm_status setup_transforms(abm_plan_s* pl, Group& g, hipStream_t st)
                                                    st)) != hipSuccess)
             return hip_fail(e, "weight spectra");
     }
-    if (s == ABM_ENOMEM) {
-        (void)hipGetLastError();
-        dev_free(g.spec);
-        dev_free(g.fpart);
-        g.spec = g.fpart = nullptr;
-        g.fft = false;
-        return ABM_OK;
-    }
     return s;
 }
 
-abm_status batch_setup(abm_plan_s* pl)
+// Groups, device memory and schedule; transforms: old history of the double
+// column tiles by transforms.
+static abm_status batch_build(abm_plan_s* pl, bool transforms)
 {
     hipStream_t st = pl->ctx->stream;
     abm_status s = choose_blocking(pl, pl->shape.data(), pl->B);
@@ -447,7 +440,7 @@ abm_status batch_setup(abm_plan_s* pl)
             if ((s = ensure_reduced_weights(pl->tables[g.table[c]], g.prec, st))) return s;
             W[c] = &pl->tables[g.table[c]];
         }
-        g.fft = !g.narrow && g.prec == ABM_FAR_FP64;
+        g.fft = transforms && !g.narrow && g.prec == ABM_FAR_FP64;
         if (g.fft && (s = setup_transforms(pl, g, st))) return s;
         if ((s = alloc_group(g, L, (int)group_far_split_max(g, L, kchunk, pl->max_split), st))) return s;
         gdev.push_back(group_dev(g, W));
@@ -600,6 +593,24 @@ abm_status batch_setup(abm_plan_s* pl)
         if (e != hipSuccess) return hip_fail(e, "far stream");
     }
     return ABM_OK;
+}
+
+// The spectra are optional and take about twice their history's bytes: a plan
+// that does not fit with them is made again from nothing without them, so the
+// device memory a plan needs is that of the direct products.  All groups go
+// back together, so that one plan has one chunk size for its double tiles.
+abm_status batch_setup(abm_plan_s* pl)
+{
+    const int64_t left = alloc_left();
+    abm_status s = batch_build(pl, true);
+    bool used = false;
+    for (const Group& g : pl->groups) used = used || g.fft;
+    if (s != ABM_ENOMEM || !used) return s;
+    (void)hipGetLastError();
+    batch_teardown(pl);
+    for (auto& t : pl->tables) free_reduced(t);
+    set_alloc_left(left);
+    return batch_build(pl, false);
 }
 
 namespace {
