@@ -134,8 +134,11 @@ typedef struct abm_result {
  * ABM_BLOCK_L / ABM_KCHUNK / ABM_MAX_SPLIT / ABM_NARROW environment override). */
 typedef struct abm_tuning {
     int32_t block_L;            /* near-band block length: 64 (double far field only), 128, 256, 512 */
-    int32_t kchunk;             /* history rows per far-field chunk: a multiple of 512 (lowered
-                                   until the chunk's weight window fits the LDS) */
+    int32_t kchunk;             /* history rows per far-field chunk of the column tiles: a multiple
+                                   of 512 (lowered until the chunk's weight window fits the LDS),
+                                   or 256 where every problem's far field is double.  Default 256
+                                   there (2048 in a plan that has no room for its spectra), else
+                                   2048; double tiles beside other precisions take 256 */
     int32_t max_split;          /* most far-field workgroups along the history per column tile */
     int32_t column_tiles_only;  /* 1: no blocked convolution for narrow groups */
 } abm_tuning;

@@ -171,8 +171,6 @@ struct FarItem {
                            // padded to the tile width except in narrow groups;
                            // all columns of a per-component group)
     int64_t k0;            // double column tiles: history 1 .. k0 is left to the transforms
-    int32_t kc;            // chunk rows of this item (0: the launch's)
-    int32_t pad_;
 };
 
 // Transforms of one group (or component) for superblock Q.

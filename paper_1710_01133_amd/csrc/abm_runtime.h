@@ -66,6 +66,7 @@ struct Group {
     double* part[2] = {nullptr, nullptr};   // far partials by block parity
     size_t part_half = 0;           // doubles per partial buffer
     int nsplit_cap = 0;             // partial slices each buffer holds
+    int kchunk = 0;                 // rows per far chunk (0: the schedule's)
     bool fft = false;               // double column tiles of a batch: history before the
                                     // superblock by transforms
     double* spec = nullptr;
@@ -197,7 +198,6 @@ void block_items(const Group& g, int gi, int64_t m, int L, int kchunk, int max_s
                  const std::vector<int64_t>& memberN, std::vector<FarItem>* far,
                  std::vector<ChainItem>* chain);
 int64_t group_far_split_max(const Group& g, int L, int kchunk, int max_split);
-abm_status choose_blocking(abm_plan_s* pl, const abm_problem* probs, int B);
 abm_status serve_create(abm_ctx* ctx);
 void serve_shutdown(abm_ctx* ctx);
 

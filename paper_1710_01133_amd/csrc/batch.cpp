@@ -259,7 +259,6 @@ void block_items(const Group& g, int gi, int64_t m, int L, int kchunk, int max_s
         it.kfar = (mf - 1) * L;
         it.mL = mf * L;
         it.k0 = direct_from(g, mf * L, L);
-        it.kc = g.fft ? kFftChunk : 0;
         it.nsplit = group_split_plan(g, it.kfar - it.k0, L, kchunk, max_split, &it.nchunks,
                                      &it.chunks_per_split);
         const int64_t na = active(mf);
@@ -317,7 +316,7 @@ int group_split_plan(const Group& g, int64_t kfar, int L, int kchunk, int max_sp
     if (g.narrow)
         return hankel_split_plan(kfar, L, g.split_cap > 0 ? g.split_cap : max_split, nchunks,
                                  chunks_per_split);
-    return far_split_plan(kfar, g.fft ? kFftChunk : kchunk, max_split, nchunks, chunks_per_split);
+    return far_split_plan(kfar, g.kchunk ? g.kchunk : kchunk, max_split, nchunks, chunks_per_split);
 }
 
 int64_t group_far_split_max(const Group& g, int L, int kchunk, int max_split)
@@ -325,11 +324,12 @@ int64_t group_far_split_max(const Group& g, int L, int kchunk, int max_split)
     const int64_t nblocks = (g.nmax + L - 1) / L;
     const int64_t kfar_max = nblocks >= 2 ? (nblocks - 2) * L : 0;   // far(m) covers (m-1)L
     if (g.narrow) return hankel_split_bound(kfar_max, L, g.split_cap > 0 ? g.split_cap : max_split);
-    if (g.fft) return far_split_bound(std::min<int64_t>(kfar_max, kFftRows), kFftChunk, max_split);
-    return far_split_bound(kfar_max, kchunk, max_split);
+    return far_split_bound(g.fft ? std::min<int64_t>(kfar_max, kFftRows) : kfar_max,
+                           g.kchunk ? g.kchunk : kchunk, max_split);
 }
 
-abm_status choose_blocking(abm_plan_s* pl, const abm_problem* probs, int B)
+// transforms: old history of the double column tiles by transforms
+static abm_status choose_blocking(abm_plan_s* pl, const abm_problem* probs, int B, bool transforms)
 {
     const abm_tuning& T = pl->tune;
     int L = T.block_L ? T.block_L : env_int("ABM_BLOCK_L", 256);
@@ -340,14 +340,22 @@ abm_status choose_blocking(abm_plan_s* pl, const abm_problem* probs, int B)
         if (probs[i].far_prec == ABM_FAR_I8 && L > 256)
             return fail(ABM_EINVAL, "problem %d: the int8 far field needs block length 128 or 256", i);
     }
-    int kchunk = T.kchunk ? T.kchunk : env_int("ABM_KCHUNK", 2048);
-    if (kchunk < 512 || kchunk % 512 || kchunk > (1 << 20))
-        return fail(ABM_EINVAL, "history chunk %d must be a multiple of 512 (at most 2^20)", kchunk);
+    bool all_double = true;
+    for (int i = 0; i < B; ++i) all_double = all_double && probs[i].far_prec == ABM_FAR_FP64;
+    // beside the transforms the direct products cover at most kFftRows rows:
+    // short chunks spread them over more workgroups (64 oscillators of 8192
+    // steps: 2.58 ms at 256 rows, 4.68 at 2048 without transforms)
+    int kchunk = T.kchunk ? T.kchunk : env_int("ABM_KCHUNK", all_double && transforms ? kFftChunk : 2048);
+    if ((kchunk < 512 || kchunk % 512 || kchunk > (1 << 20)) && !(all_double && kchunk == kFftChunk))
+        return fail(ABM_EINVAL, "history chunk %d must be a multiple of 512 (at most 2^20)%s", kchunk,
+                    all_double ? ", or 256" : "");
     // largest chunk whose LDS footprint fits every precision used
     for (int prec : kBlockedPrecs)
         while (kchunk > 512 && far_lds_bytes(L, kchunk, prec) > kMaxLds) kchunk -= 512;
     pl->L = L;
     pl->kchunk = kchunk;
+    // a plan of several precisions: its chunk is that of the reduced ones
+    pl->kchunk64 = all_double || !transforms ? kchunk : kFftChunk;
     pl->max_split = T.max_split ? T.max_split : env_int("ABM_MAX_SPLIT", 8);
     if (pl->max_split < 1 || pl->max_split > 4096)
         return fail(ABM_EINVAL, "split count %d out of range 1..4096", pl->max_split);
@@ -389,7 +397,7 @@ static abm_status setup_transforms(abm_plan_s* pl, Group& g, hipStream_t st)
 static abm_status batch_build(abm_plan_s* pl, bool transforms)
 {
     hipStream_t st = pl->ctx->stream;
-    abm_status s = choose_blocking(pl, pl->shape.data(), pl->B);
+    abm_status s = choose_blocking(pl, pl->shape.data(), pl->B, transforms);
     if (s) return s;
     const int L = pl->L, kchunk = pl->kchunk;
 
@@ -440,15 +448,12 @@ static abm_status batch_build(abm_plan_s* pl, bool transforms)
             if ((s = ensure_reduced_weights(pl->tables[g.table[c]], g.prec, st))) return s;
             W[c] = &pl->tables[g.table[c]];
         }
+        if (!g.narrow && g.prec == ABM_FAR_FP64) g.kchunk = pl->kchunk64;
         g.fft = transforms && !g.narrow && g.prec == ABM_FAR_FP64;
         if (g.fft && (s = setup_transforms(pl, g, st))) return s;
         if ((s = alloc_group(g, L, (int)group_far_split_max(g, L, kchunk, pl->max_split), st))) return s;
         gdev.push_back(group_dev(g, W));
     }
-
-    pl->kchunk64 = kFftChunk;
-    for (const Group& g : pl->groups)
-        if (!g.narrow && g.prec == ABM_FAR_FP64 && !g.fft) pl->kchunk64 = kchunk;
 
     // static tick schedule: far items by precision class, chain items by rhs
     const int ngroups = (int)pl->groups.size();

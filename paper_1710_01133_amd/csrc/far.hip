@@ -9,8 +9,7 @@
 // with F_k the time-major history row (all columns = trajectory components).
 // The k = 0 terms (b_n f_0, c_n f_0) and the near band are added by the chain
 // kernel.  In a batch the products start at k = k0 + 1, the history since the
-// block's superblock began (far_fft.hip takes the older one), in chunks of
-// 256 rows.
+// block's superblock began (far_fft.hip takes the older one).
 //
 // Tiling: one workgroup computes all 2L rows for 16*NT columns over a fixed
 // range of history chunks [k_lo, k_hi) (chunk boundaries and their grouping
@@ -39,7 +38,6 @@ __global__ __launch_bounds__(256) void k_far_f64(const GroupDev* groups, const F
     constexpr int TN = 16 * NT;      // columns per workgroup
     FarArgs A;
     if (!far_view(groups, items, kchunk, L, A)) return;
-    if (const int kc = items[blockIdx.z].kc) A.kchunk = kc;
     extern __shared__ double sm[];
     const int win = L + A.kchunk;    // weight window length (padded)
     double* wb = sm;                 // b window

@@ -27,6 +27,7 @@ struct Tuner {
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     std::vector<abm_tune_trial> trials;
     std::vector<int32_t> narrow;            // narrow groups seen by each trial
+    std::vector<int32_t> tiles;             // groups in column tiles
 
     // one trial; returns its status (recorded with the time)
     abm_status run(const abm_tuning& cfg)
@@ -34,7 +35,7 @@ struct Tuner {
         abm_tune_trial tr{};
         tr.cfg = cfg;
         tr.ms = -1.0;
-        int32_t tr_narrow = 0;
+        int32_t tr_narrow = 0, tr_tiles = 0;
         abm_plan_t* pl = nullptr;
         abm_status s = abm_plan_tuned(ctx, probs, B, &cfg, &pl);
         if (s == ABM_OK) {
@@ -52,6 +53,7 @@ struct Tuner {
             abm_stats st{};
             if (s == ABM_OK) s = abm_solve_batch(pl, probs, B, outs.data(), &st);
             tr_narrow = st.narrow_groups;
+            tr_tiles = st.n_groups - st.narrow_groups;
             if (s == ABM_OK && (e = hipEventRecord(ev1, ctx->stream)) != hipSuccess) s = hip_fail(e, "event");
             if (s == ABM_OK) s = abm_plan_check(pl);
             float ms = 0.f;
@@ -62,6 +64,7 @@ struct Tuner {
         tr.status = s;
         trials.push_back(tr);
         narrow.push_back(tr_narrow);
+        tiles.push_back(tr_tiles);
         return s;
     }
 
@@ -136,7 +139,8 @@ extern "C" abm_status abm_autotune(abm_ctx* ctx, const abm_problem* probs, int32
         (void)T.run(c);
     }
     // stage 2: split count (fewest partial slices first: a larger count has to
-    // win by the margin), stage 3: chunk, at the best so far
+    // win by the margin), stage 3: chunk, at the best so far, where column
+    // tiles read it (double ones sum at most a superblock of 2048 rows)
     const int splits[] = {2, 4, 16};
     for (int sp : splits) {
         const abm_tune_trial* b = T.best();
@@ -145,10 +149,11 @@ extern "C" abm_status abm_autotune(abm_ctx* ctx, const abm_problem* probs, int32
         c.max_split = sp;
         (void)T.run(c);
     }
-    const int chunks[] = {1024, 4096, 8192};
+    const std::vector<int> chunks = all_fp64 ? std::vector<int>{512, 1024, 2048}
+                                             : std::vector<int>{1024, 4096, 8192};
     for (int kc : chunks) {
         const abm_tune_trial* b = T.best();
-        if (!b || !in_budget()) break;
+        if (!b || !in_budget() || T.tiles[b - T.trials.data()] == 0) break;
         abm_tuning c = b->cfg;
         c.kchunk = kc;
         (void)T.run(c);
