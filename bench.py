@@ -235,7 +235,7 @@ def small_batch_leg(abm, torch, inputs, ctx, steps=20):
         plan.graph(mode == "graph")
         dt, st = time_batch(abm, torch, plan, probs, ys, steps, 2)
         res[mode + "_ms"] = dt * 1e3
-        res["launches"] = st["far_launches"] + st["chain_launches"]
+        res["launches"] = st["far_launches"] + st["chain_launches"] + st["transform_launches"]
     plan.close()
     return res
 

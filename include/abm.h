@@ -109,14 +109,15 @@ typedef struct abm_stats {
     int32_t block_L;      /* near-band block length used by abm_solve_batch */
     int32_t n_groups;     /* trajectory groups sharing one weight table */
     int64_t history_macs; /* sum over trajectories of d*N*(N+1)/2 */
-    int64_t far_macs;     /* multiply-adds issued by the far-field kernels (useful ones) */
-    int32_t far_launches; /* far-field kernel launches enqueued */
+    int64_t far_macs;     /* multiply-adds issued by the far-field products (useful ones) */
+    int32_t far_launches; /* launches of far-field products enqueued */
     int32_t chain_launches;
-    double far_ms;        /* summed device time of the far-field launches (timing on, else 0) */
+    double far_ms;        /* summed device time of those far_launches (timing on, else 0) */
     double chain_ms;      /* summed device time of the chain launches (timing on, else 0) */
     int32_t narrow_groups; /* groups of at most a few columns whose far field runs as a
                               blocked convolution instead of column tiles */
-    int32_t reserved_;
+    int32_t transform_launches; /* launches that transform old history (double column tiles):
+                                   not among far_launches, far_ms and far_macs */
 } abm_stats;
 
 typedef struct abm_result {

@@ -42,7 +42,7 @@ class AbmStats(ctypes.Structure):
                 ("history_macs", ctypes.c_int64), ("far_macs", ctypes.c_int64),
                 ("far_launches", ctypes.c_int32), ("chain_launches", ctypes.c_int32),
                 ("far_ms", ctypes.c_double), ("chain_ms", ctypes.c_double),
-                ("narrow_groups", ctypes.c_int32), ("reserved_", ctypes.c_int32)]
+                ("narrow_groups", ctypes.c_int32), ("transform_launches", ctypes.c_int32)]
 
 
 class AbmResult(ctypes.Structure):

@@ -146,6 +146,7 @@ struct abm_plan_s {
     hipGraph_t graph = nullptr;
     hipGraphExec_t graph_exec = nullptr;
     int64_t graph_far_launches = 0;
+    int64_t graph_transform_launches = 0;
     int64_t graph_chain_launches = 0;
 };
 

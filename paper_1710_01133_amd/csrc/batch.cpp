@@ -628,9 +628,9 @@ namespace {
 struct TickEnqueuer {
     abm_plan_s* pl;
     bool timing;
-    std::vector<std::pair<int, int>> tev;   // (0 far | 1 chain, index of the start event)
+    std::vector<std::pair<int, int>> tev;   // (0 far | 1 chain | 2 transforms, index of the start event)
     size_t ev_used = 0, sync_used = 0;
-    int64_t far_launches = 0, chain_launches = 0;
+    int64_t far_launches = 0, chain_launches = 0, transform_launches = 0;
 
     TickEnqueuer(abm_plan_s* p, bool t) : pl(p), timing(t) {}
 
@@ -705,12 +705,12 @@ struct TickEnqueuer {
                 if (!alt && ev_chain_prev && (e = hipStreamWaitEvent(sf, ev_chain_prev, 0)) != hipSuccess)
                     return hip_fail(e, "stream wait");
                 if (fs.count) {
-                    e = timed(0, sf, [&]() {
+                    e = timed(2, sf, [&]() {
                         return launch_far_fft(pl->groups_dev, pl->fft_items_dev + fs.offset, fs.count,
                                               fs.max_cols, L, pl->fft_tw, sf);
                     });
                     if (e != hipSuccess) return hip_fail(e, "transform launch");
-                    far_launches += 2;
+                    transform_launches += 2;
                 }
                 for (int cls = 0; cls < kFarClasses; ++cls) {
                     const Span& sp = pl->far_spans[t * kFarClasses + cls];
@@ -813,6 +813,7 @@ abm_status capture_ticks(abm_plan_s* pl)
     }
     pl->graph = g;
     pl->graph_far_launches = q.far_launches;
+    pl->graph_transform_launches = q.transform_launches;
     pl->graph_chain_launches = q.chain_launches;
     return ABM_OK;
 }
@@ -918,11 +919,13 @@ extern "C" abm_status abm_solve_batch(abm_plan_t* pl, const abm_problem* probs, 
         e = hipGraphLaunch(pl->graph_exec, st);
         if (e != hipSuccess) return hip_fail(e, "graph launch");
         S.far_launches = pl->graph_far_launches;
+        S.transform_launches = (int32_t)pl->graph_transform_launches;
         S.chain_launches = pl->graph_chain_launches;
     } else {
         TickEnqueuer q(pl, pl->timing);
         if ((s = q.run(st))) return s;
         S.far_launches = q.far_launches;
+        S.transform_launches = (int32_t)q.transform_launches;
         S.chain_launches = q.chain_launches;
         if (pl->timing && !q.tev.empty()) {
             e = hipStreamSynchronize(st);
@@ -931,7 +934,7 @@ extern "C" abm_status abm_solve_batch(abm_plan_t* pl, const abm_problem* probs, 
                 float ms = 0.f;
                 e = hipEventElapsedTime(&ms, pl->events[te.second], pl->events[te.second + 1]);
                 if (e != hipSuccess) return hip_fail(e, "event time");
-                (te.first == 0 ? S.far_ms : S.chain_ms) += ms;
+                if (te.first < 2) (te.first == 0 ? S.far_ms : S.chain_ms) += ms;
             }
         }
     }
