@@ -119,7 +119,6 @@ struct CompWeights {
     const float* a32;
     const uint16_t* bh[3]; // bf16 split terms (far_prec bf16x3 / bf16x6)
     const uint16_t* ah[3];
-    const double* fft;     // spectra of the weights by lag (far_fft.hip), or null
     double alpha;
 };
 
@@ -140,8 +139,6 @@ struct GroupDev {
     int64_t rows;          // history rows allocated
     double* accn;          // [member][2][d][L] sums carried into the next block
     double* part[2];       // far partials [split][col][2L], by block parity
-    double* spec;          // spectra of the history blocks [p][ldF][kFftStride] (complex), or null
-    double* fpart;         // sums of the transforms [superblock parity][block][ldF][2L]
     const TrajDesc* traj;  // members
     int32_t d;
     int32_t narrow;        // 1: few columns, far field by the blocked convolution,
@@ -151,6 +148,10 @@ struct GroupDev {
     int32_t deriv;         // bit i: component i has order above 1 (start term x0 + t x1)
     uint32_t* status;      // status word of this group's own (kStatus* bits), or null: the
                            // chain then raises the launch's word
+    // double column tiles with transforms of old history (null otherwise)
+    const double* wspec[4];   // component i's weight spectra by lag
+    double* spec;          // spectra of the history blocks [p][ldF][kFftStride] (complex)
+    double* fpart;         // sums of the transforms [superblock parity][block][ldF][2L]
 };
 
 // Far field of one group (or of one component of a group whose components
@@ -160,7 +161,8 @@ struct FarItem {
     int32_t ncoltiles;     // active columns / tile width (narrow: product tiles)
     int32_t nchunks;       // ceil(kfar / kchunk) (narrow: chunks of shifts)
     int32_t chunks_per_split;
-    int32_t nsplit;        // partial slices written
+    int32_t nsplit;        // partial slices written (one without chunks where a superblock
+                           // begins: the transforms' sums)
     int32_t comp;          // weight tables used: the group's w[comp]
     int32_t coff;          // first history column of the item (a multiple of 16
                            // unless the group is narrow)
@@ -188,8 +190,6 @@ struct ChainItem {
     int32_t member;
     int32_t nsplit;        // far partial slices of this block (0 when m < 2)
     int32_t kind;          // chain_kind of the group
-    int32_t fslice;        // 1 + slice of the group's fpart that holds this block's sums; 0: none
-    int32_t pad_;
     int64_t mL;
     int64_t ldP;
 };

@@ -186,7 +186,7 @@ GroupDev group_dev(const Group& g, const WeightTable* const W[4])
             w.ah[i] = W[c]->ah[i];
         }
         w.alpha = W[c]->alpha;
-        w.fft = W[c]->fft;
+        d.wspec[c] = W[c]->fft;
     }
     for (int i = 0; i < 3; ++i) d.Fh[i] = g.Fh[i];
     d.Fsc = g.Fsc;
@@ -253,14 +253,14 @@ void block_items(const Group& g, int gi, int64_t m, int L, int kchunk, int max_s
         return cnt;
     };
     const int64_t mf = m + 1;
-    if (far && mf < nblocks && mf >= 2 && (mf - 1) * L > direct_from(g, mf * L, L)) {
+    if (far && mf < nblocks && mf >= 2) {
         FarItem it{};
         it.group = gi;
         it.kfar = (mf - 1) * L;
         it.mL = mf * L;
         it.k0 = direct_from(g, mf * L, L);
-        it.nsplit = group_split_plan(g, it.kfar - it.k0, L, kchunk, max_split, &it.nchunks,
-                                     &it.chunks_per_split);
+        it.nsplit = std::max(1, group_split_plan(g, it.kfar - it.k0, L, kchunk, max_split, &it.nchunks,
+                                                 &it.chunks_per_split));
         const int64_t na = active(mf);
         if (g.per_comp) {
             // one item per component: its column block, its weight tables;
@@ -287,9 +287,9 @@ void block_items(const Group& g, int gi, int64_t m, int L, int kchunk, int max_s
     }
     if (chain && m < nblocks) {
         int nsp = 0, nc = 0, cps = 0;
-        const int64_t k0 = direct_from(g, m * L, L);
-        if (m >= 2 && (m - 1) * L > k0)
-            nsp = group_split_plan(g, (m - 1) * L - k0, L, kchunk, max_split, &nc, &cps);
+        if (m >= 2)
+            nsp = std::max(1, group_split_plan(g, (m - 1) * L - direct_from(g, m * L, L), L, kchunk,
+                                               max_split, &nc, &cps));
         const int32_t na = active(m);
         const int64_t ldP = g.per_comp ? g.ldF
                           : g.narrow  ? (int64_t)na * g.d
@@ -300,9 +300,6 @@ void block_items(const Group& g, int gi, int64_t m, int L, int kchunk, int max_s
             c.member = j;
             c.kind = chain_kind(g.rhs, g.per_comp);
             c.nsplit = nsp;
-            const int64_t Q = m * L / kFftRows;
-            if (g.fft && Q > 0)
-                c.fslice = (int32_t)(1 + (Q & 1) * (kFftRows / L) + (m * L - Q * kFftRows) / L);
             c.mL = m * L;
             c.ldP = ldP;
             chain->push_back(c);
@@ -691,7 +688,10 @@ struct TickEnqueuer {
         // far(t+1) overwrites the slices of block t-1 only after chain(t-1), the
         // stream's previous work, has read them.
         const bool alt = pl->overlap && env_int("ABM_ALT_STREAMS", 1) != 0;
-        hipEvent_t ev_chain_prev = nullptr, ev_far_prev = nullptr;
+        // The transforms of a superblock are read by the far fields of all its
+        // blocks: the next tick's runs on the other stream and waits by event,
+        // the later ones follow the chains between.
+        hipEvent_t ev_chain_prev = nullptr, ev_far_prev = nullptr, ev_fft = nullptr;
         for (int64_t t = 0; t < pl->ticks; ++t) {
             hipStream_t sc = st, sf = s1;
             if (alt && (t & 1)) std::swap(sc, sf);
@@ -704,6 +704,9 @@ struct TickEnqueuer {
             if (any_far) {
                 if (!alt && ev_chain_prev && (e = hipStreamWaitEvent(sf, ev_chain_prev, 0)) != hipSuccess)
                     return hip_fail(e, "stream wait");
+                if (alt && ev_fft && (e = hipStreamWaitEvent(sf, ev_fft, 0)) != hipSuccess)
+                    return hip_fail(e, "stream wait");
+                ev_fft = nullptr;
                 if (fs.count) {
                     e = timed(2, sf, [&]() {
                         return launch_far_fft(pl->groups_dev, pl->fft_items_dev + fs.offset, fs.count,
@@ -711,6 +714,9 @@ struct TickEnqueuer {
                     });
                     if (e != hipSuccess) return hip_fail(e, "transform launch");
                     transform_launches += 2;
+                    ev_fft = sync_event();
+                    if (!ev_fft || (e = hipEventRecord(ev_fft, sf)) != hipSuccess)
+                        return fail(ABM_EDEVICE, "transform event");
                 }
                 for (int cls = 0; cls < kFarClasses; ++cls) {
                     const Span& sp = pl->far_spans[t * kFarClasses + cls];

@@ -45,7 +45,6 @@ struct ChainArgs {
     int64_t rows;
     bool narrow;           // F32 time-major [k][ldF] instead of column-blocked
     gptr<const double> part;
-    gptr<const double> fpart;   // the block's sums from the transforms, or null
     int64_t ldP;
     int64_t mL;
     int32_t nchunks;
@@ -77,8 +76,6 @@ __device__ __forceinline__ void chain_view(const GroupDev& G, const ChainItem& i
     A.rows = G.rows;
     A.narrow = G.narrow != 0;
     A.part = as_global((const double*)G.part[(it.mL / L) & 1]);
-    A.fpart = it.fslice ? as_global((const double*)G.fpart) + (size_t)(it.fslice - 1) * G.ldF * (2 * L)
-                        : nullptr;
     A.ldP = it.ldP;
     A.mL = it.mL;
     A.nchunks = it.nsplit;
@@ -286,10 +283,10 @@ __device__ __forceinline__ void chain_block(const GroupDev& G, const ChainItem& 
 #pragma unroll
         for (int q = 0; q < Q; ++q) sp[q] = sc[q] = 0.0;
         const gptr<const double> pc0 = A.part + (size_t)comp_col(T, i) * (2 * L) + r0;
-        auto load_from = [&](gptr<const double> at, double* v) {
+        auto load_rows = [&](size_t off, double* v) {
             if constexpr (Q % 2 == 0) {
                 typedef double d2 __attribute__((ext_vector_type(2)));
-                const gptr<const d2> src = (gptr<const d2>)at;
+                const gptr<const d2> src = (gptr<const d2>)(pc0 + off);
 #pragma unroll
                 for (int q = 0; q < Q / 2; ++q) {
                     const d2 x = src[q];
@@ -298,10 +295,9 @@ __device__ __forceinline__ void chain_block(const GroupDev& G, const ChainItem& 
                 }
             } else {
 #pragma unroll
-                for (int q = 0; q < Q; ++q) v[q] = at[q];
+                for (int q = 0; q < Q; ++q) v[q] = pc0[off + q];
             }
         };
-        auto load_rows = [&](size_t off, double* v) { load_from(pc0 + off, v); };
         int ch = 0;
         for (; ch + 4 <= A.nchunks; ch += 4) {
             double vp[4][Q], vc[4][Q];
@@ -322,17 +318,6 @@ __device__ __forceinline__ void chain_block(const GroupDev& G, const ChainItem& 
             double vp[Q], vc[Q];
             load_rows(ch * sstride, vp);
             load_rows(ch * sstride + L, vc);
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                sp[q] += vp[q];
-                sc[q] += vc[q];
-            }
-        }
-        if (A.fpart) {
-            double vp[Q], vc[Q];
-            const gptr<const double> at = A.fpart + (size_t)comp_col(T, i) * (2 * L) + r0;
-            load_from(at, vp);
-            load_from(at + L, vc);
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
                 sp[q] += vp[q];

@@ -30,8 +30,10 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 
 constexpr int kKS = 16;   // history rows per LDS stage
 
+// Two waves per SIMD: left to itself the compiler hoists the loads of the
+// transforms' sums and takes 272 registers (forcing sweep 44.1 against 38.4 ms).
 template <int MT, int NT>
-__global__ __launch_bounds__(256) void k_far_f64(const GroupDev* groups, const FarItem* items,
+__global__ __launch_bounds__(256, 2) void k_far_f64(const GroupDev* groups, const FarItem* items,
                                                  int kchunk)
 {
     constexpr int L = 32 * MT;       // block length
@@ -142,6 +144,18 @@ __global__ __launch_bounds__(256) void k_far_f64(const GroupDev* groups, const F
         }
     }
 
+    // The first slice also takes the sums of the transforms over the history
+    // before this superblock (their columns are the group's).  Read by the
+    // chains instead, they cost every other precision's chains a branch and
+    // registers: circuit sweep in int8 limbs 106.5 against 105.8 ms.
+    const FarItem it = items[blockIdx.z];
+    const int64_t Q = mL / kFftRows;
+    const double* const sums = groups[it.group].fpart;
+    const bool add = sums && Q > 0 && blockIdx.y == 0;
+    const int64_t block = (Q & 1) * (kFftRows / L) + (mL - Q * kFftRows) / L;
+    const gptr<const double> old =
+        add ? as_global(sums) + ((size_t)block * A.ldF + it.coff) * (2 * L) : nullptr;
+
     // FFpart[split][col][2L].  The double 16x16x4 product returns row
     // lk + 4v of column li of the tile in register v of lane (li, lk).
     const gptr<double> out = A.part + (size_t)blockIdx.y * A.ldP * (2 * L);
@@ -151,7 +165,12 @@ __global__ __launch_bounds__(256) void k_far_f64(const GroupDev* groups, const F
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
             const int col = col0 + j * 16 + li;
-            const gptr<double> o = out + (size_t)col * (2 * L) + prow + i * 16 + lk;
+            const size_t at = (size_t)col * (2 * L) + prow + i * 16 + lk;
+            const gptr<double> o = out + at;
+            if (add) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[i][j][v] += old[at + 4 * v];
+            }
 #pragma unroll
             for (int v = 0; v < 4; ++v) o[4 * v] = acc[i][j][v];
         }

@@ -222,7 +222,7 @@ __global__ __launch_bounds__(kThreads) void k_fft_sums(const GroupDev* groups, c
     const size_t step = (size_t)G.ldF * kFftStride;
     gptr<const cplx> f = as_global((const cplx*)G.spec) + (size_t)col * kFftStride + v;
     // lag Q - p of history block p: its weights' spectra, b then a
-    gptr<const cplx> w = as_global((const cplx*)G.w[it.comp].fft) + (size_t)(it.Q - 1) * 2 * kFftStride + v;
+    gptr<const cplx> w = as_global((const cplx*)G.wspec[it.comp]) + (size_t)(it.Q - 1) * 2 * kFftStride + v;
     cplx yb[8], ya[8], mb{0.0, 0.0}, ma{0.0, 0.0};
 #pragma unroll
     for (int j = 0; j < 8; ++j) yb[j] = ya[j] = {0.0, 0.0};
