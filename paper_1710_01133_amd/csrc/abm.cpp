@@ -393,7 +393,10 @@ namespace abm {
 // behind the sequencer at the end of the run (200000-step oscillator, 46
 // chunks each: 0.111 against 0.100 us per step), more only add traffic on the
 // flags (linear, 65536 steps: 0.056 at 16 chunks each, 0.063 at 8).
-constexpr int kAloneBlocks = 32;
+// Double-double: the waves beside its sequencer fall behind earlier (us per
+// step alone / with 3 workgroups, 1024 steps: linear 0.456 / 0.464, oscillator
+// 1.056 / 1.058; 2048 steps: 0.595 / 0.445 and 1.249 / 1.037).
+constexpr int kAloneBlocks = 32, kAloneBlocksDd = 16;
 constexpr int kWorkerChunks = 16;
 
 abm_status plain_shape(const abm_problem& p, int n_cu, PlainShape* out)
@@ -414,7 +417,7 @@ abm_status plain_shape(const abm_problem& p, int n_cu, PlainShape* out)
     const int forced = env_int("ABM_PLAIN_G", 0);
     const bool fits = (dd ? plain_dd_chain_lds(d, pc, chunks, true) : plain_chain_lds(d, pc, chunks, true)) <= kPlainLds;
     PlainShape sh{};
-    if (fits && (forced == 1 || (forced <= 0 && chunks <= kAloneBlocks))) {
+    if (fits && (forced == 1 || (forced <= 0 && chunks <= (dd ? kAloneBlocksDd : kAloneBlocks)))) {
         *out = sh;
         return ABM_OK;
     }

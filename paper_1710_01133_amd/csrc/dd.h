@@ -119,6 +119,40 @@ __host__ __device__ __forceinline__ dd dd_div_d(dd x, double y)
 // acc + w * f
 __host__ __device__ __forceinline__ dd dd_fma(dd w, dd f, dd acc) { return dd_add(acc, dd_mul(w, f)); }
 
+// acc + w * f in a running sum, |w f| small beside |acc|: the product's head
+// and then the two heads' error enter exactly (two_sum), so that one rounding
+// of the low part's size is left where dd_fma has two -- 21 operations for its
+// 27; rms error of a sum of 2048 terms 0.76 to 0.83 of dd_fma's.
+__host__ __device__ __forceinline__ dd dd_mac(dd w, dd f, dd acc)
+{
+    dd p = two_prod(w.hi, f.hi);
+    p.lo = fma(w.hi, f.lo, fma(w.lo, f.hi, p.lo));
+    const dd s = two_sum(acc.hi, p.hi);
+    const dd t = two_sum(acc.lo, s.lo);
+    return fast_two_sum(s.hi, t.hi + (t.lo + p.lo));
+}
+
+// The same in 18 operations: the low parts by fast_two_sum, exact where acc's
+// is the larger (rms 0.83 to 0.91 of dd_fma's).
+__host__ __device__ __forceinline__ dd dd_mac18(dd w, dd f, dd acc)
+{
+    dd p = two_prod(w.hi, f.hi);
+    p.lo = fma(w.hi, f.lo, fma(w.lo, f.hi, p.lo));
+    const dd s = two_sum(acc.hi, p.hi);
+    const dd t = fast_two_sum(acc.lo, s.lo);
+    return fast_two_sum(s.hi, t.hi + (t.lo + p.lo));
+}
+
+// And in 15, two roundings of the low part's size (rms up to 1.14 of
+// dd_fma's): for sums that are small beside what they are added to.
+__host__ __device__ __forceinline__ dd dd_mac15(dd w, dd f, dd acc)
+{
+    dd p = two_prod(w.hi, f.hi);
+    p.lo = fma(w.hi, f.lo, fma(w.lo, f.hi, p.lo));
+    const dd s = two_sum(acc.hi, p.hi);
+    return fast_two_sum(s.hi, acc.lo + (s.lo + p.lo));
+}
+
 __host__ __device__ __forceinline__ bool dd_le(dd x, double c) { return x.hi < c || (x.hi == c && x.lo <= 0.0); }
 __host__ __device__ __forceinline__ bool dd_ge(dd x, double c) { return x.hi > c || (x.hi == c && x.lo >= 0.0); }
 __host__ __device__ __forceinline__ bool dd_isfinite(dd x) { return isfinite(x.hi) && isfinite(x.lo); }

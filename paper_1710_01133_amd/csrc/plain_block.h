@@ -25,7 +25,7 @@
 // issues every 4.2 cycles whether or not it depends on the one before, and so
 // does every other instruction), 0.053 us per step for the linear equation,
 // 0.100 for the oscillator, 0.138 for Lorenz, at any length (double-double:
-// 0.45, 1.00, 1.4); one reduction per step took 0.91 (8192 steps of the linear
+// 0.43, 1.02, 1.43); one reduction per step took 0.91 (8192 steps of the linear
 // equation, one workgroup) and 2.9 (200000 steps of the oscillator;
 // double-double 2.4 and 5.0).  Hence the 64 rows unrolled (a lane index
 // in an SGPR costs a readlane twice the time: 0.135 us per step of the
@@ -88,11 +88,15 @@ struct Num<double> {
     static constexpr bool kUnroll = true;    // the sequencer's 64 rows unrolled
     static __device__ __forceinline__ double zero() { return 0.0; }
     static __device__ __forceinline__ double mac(double w, double f, double acc) { return fma(w, f, acc); }   // acc + w f
+    // the same for the newest block's terms, and for the state's update
+    static __device__ __forceinline__ double mac_near(double w, double f, double acc) { return fma(w, f, acc); }
+    static __device__ __forceinline__ double mac_state(double w, double f, double acc) { return fma(w, f, acc); }
     static __device__ __forceinline__ double mul_add(double a, double b, double c) { return fma(a, b, c); }
     // mac for a step's newest term, w = newest_weight(weight): as a
     // multiply-add of -f it takes acc from scalar registers
     static __device__ __forceinline__ double newest_weight(double w) { return -w; }
     static __device__ __forceinline__ double newest(double w, double f, double acc) { return fma(w, -f, acc); }
+    static __device__ __forceinline__ double newest_predictor(double w, double f, double acc) { return fma(w, -f, acc); }
     static __device__ __forceinline__ double add(double a, double b) { return a + b; }
     static __device__ __forceinline__ double mul(double a, double b) { return a * b; }
     static __device__ __forceinline__ double of(double x) { return x; }
@@ -526,22 +530,22 @@ __device__ __forceinline__ void chain(const PlainArgs& A, T* sm, uint32_t* s_abo
                     // lane r's value broadcast, the newest term added to it
 #pragma unroll
                     for (int i = 0; i < D; ++i) {
-                        yP[i] = M::newest(b0[i], Fp.v[i], M::lane(M::mul_add(ha[i], P[i], base[i]), r));
+                        yP[i] = M::newest_predictor(b0[i], Fp.v[i], M::lane(M::mul_add(ha[i], P[i], base[i]), r));
                         C[i] = M::newest(a0[i], Fp.v[i], M::lane(M::mul_add(ha[i], P[D + i], base[D + i]), r));
                     }
                     M::template rhs<R, D>(p, yP, f_t, fP);
 #pragma unroll
-                    for (int i = 0; i < D; ++i) y.v[i] = M::mac(gi[i], fP[i], C[i]);
+                    for (int i = 0; i < D; ++i) y.v[i] = M::mac_state(gi[i], fP[i], C[i]);
                     // the row before's f into the later rows (row l of this
                     // block: weight l - r, of the next one: 64 + l - r; rows
                     // already done receive what is never read)
 #pragma unroll
                     for (int i = 0; i < D; ++i) {
                         const int w = PC ? i : 0;
-                        P[i] = M::mac(vc[e][w].b, Fp.v[i], P[i]);
-                        P[D + i] = M::mac(vc[e][w].a, Fp.v[i], P[D + i]);
-                        nxt[i] = M::mac(vn[e][w].b, Fp.v[i], nxt[i]);
-                        nxt[D + i] = M::mac(vn[e][w].a, Fp.v[i], nxt[D + i]);
+                        P[i] = M::mac_near(vc[e][w].b, Fp.v[i], P[i]);
+                        P[D + i] = M::mac_near(vc[e][w].a, Fp.v[i], P[D + i]);
+                        nxt[i] = M::mac_near(vn[e][w].b, Fp.v[i], nxt[i]);
+                        nxt[D + i] = M::mac_near(vn[e][w].a, Fp.v[i], nxt[D + i]);
                     }
                     M::template rhs<R, D>(p, y.v, f_t, Fp.v);
                     Fm[at + e] = Fp;
@@ -557,14 +561,26 @@ __device__ __forceinline__ void chain(const PlainArgs& A, T* sm, uint32_t* s_abo
                     group(r0, lane == 0 ? r0 : 0);
                 }
             } else {
-                for (int r0 = 0; r0 < rows; r0 += GS) group(r0, lane == 0 ? r0 : 0);
+                for (int r0 = 0; r0 < rows; r0 += GS) {
+                    // Nearly all of the loop's instructions take 8 bytes, and
+                    // those that straddle an 8-byte boundary are fetched late:
+                    // its first one is put where most of them do not (us per
+                    // step on and 4 bytes off a boundary: linear 0.429 and
+                    // 0.475, oscillator 1.145 and 1.015, Lorenz 1.53 and 1.42)
+                    if constexpr (D == 1)
+                        asm volatile(".p2align 3");
+                    else
+                        asm volatile(".p2align 3\n\ts_nop 0");
+                    __builtin_amdgcn_sched_barrier(0);
+                    group(r0, lane == 0 ? r0 : 0);
+                }
             }
             // the block's last f into the next block's rows: weight l
 #pragma unroll
             for (int i = 0; i < D; ++i) {
                 const Weight<T> w = near[(PC ? i : 0) * kNear + 64 + lane];
-                nxt[i] = M::mac(w.b, Fp.v[i], nxt[i]);
-                nxt[D + i] = M::mac(w.a, Fp.v[i], nxt[D + i]);
+                nxt[i] = M::mac_near(w.b, Fp.v[i], nxt[i]);
+                nxt[D + i] = M::mac_near(w.a, Fp.v[i], nxt[D + i]);
             }
         }
         __syncthreads();

@@ -197,22 +197,16 @@ struct Num<dd> {
     static constexpr int LR = 16;
     static constexpr bool kUnroll = false;
     static __device__ __forceinline__ dd zero() { return dd_make(0.0); }
-    // acc + w f in a running sum: the product's head enters exactly (two_sum),
-    // its error terms and the sum's rounding error enter the low part, one
-    // normalisation -- 15 operations, 27 as a normalised product and an
-    // accurate sum.  The terms of these sums do not cancel the sum's head, so
-    // both round it by about 2^-105; 14 runs against the quad oracle (1500 to
-    // 7000 steps, four systems): rms error 1.95e-31 of the scale either way.
-    static __device__ __forceinline__ dd mac(dd w, dd f, dd acc)
-    {
-        dd p = two_prod(w.hi, f.hi);
-        p.lo = fma(w.hi, f.lo, fma(w.lo, f.hi, p.lo));
-        const dd s = two_sum(acc.hi, p.hi);
-        return fast_two_sum(s.hi, acc.lo + (s.lo + p.lo));
-    }
+    // The history sums (older chunks) and the corrector round no worse than
+    // dd_fma.  The shorter form takes the at most 127 newest terms, whose sum
+    // is kept apart from the rest, and the predictor's newest term, whose
+    // rounding reaches the state only through f.
+    static __device__ __forceinline__ dd mac(dd w, dd f, dd acc) { return dd_mac(w, f, acc); }
+    static __device__ __forceinline__ dd mac_near(dd w, dd f, dd acc) { return dd_mac15(w, f, acc); }
+    static __device__ __forceinline__ dd mac_state(dd w, dd f, dd acc) { return dd_mac18(w, f, acc); }
     static __device__ __forceinline__ dd newest_weight(dd w) { return w; }
-    static __device__ __forceinline__ dd newest(dd w, dd f, dd acc) { return mac(w, f, acc); }
-    static __device__ __forceinline__ dd norm(dd acc) { return two_sum(acc.hi, acc.lo); }
+    static __device__ __forceinline__ dd newest_predictor(dd w, dd f, dd acc) { return dd_mac15(w, f, acc); }
+    static __device__ __forceinline__ dd newest(dd w, dd f, dd acc) { return dd_mac18(w, f, acc); }
     static __device__ __forceinline__ dd mul_add(dd a, dd b, dd c) { return dd_fma(a, b, c); }
     static __device__ __forceinline__ dd add(dd a, dd b) { return dd_add(a, b); }
     static __device__ __forceinline__ dd mul(dd a, dd b) { return dd_mul(a, b); }
