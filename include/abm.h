@@ -193,7 +193,9 @@ void abm_plan_destroy(abm_plan_t *plan);
 abm_status abm_plan_tuned(abm_ctx *ctx, const abm_problem *probs, int32_t B,
                           const abm_tuning *tune, abm_plan_t **out);
 
-/* The blocking a plan uses (after defaults, overrides and the LDS limit). */
+/* The blocking a plan uses (after defaults, overrides and the LDS limit);
+ * given to abm_plan_tuned it makes the same plan again.  All zeros: a plan
+ * that uses none (one trajectory that abm_solve_batch runs as abm_solve). */
 abm_status abm_plan_config(abm_plan_t *plan, abm_tuning *out);
 
 /* Choose the blocking for these problems by timing whole abm_solve_batch
@@ -202,8 +204,9 @@ abm_status abm_plan_config(abm_plan_t *plan, abm_tuning *out);
  * chain, so candidates are measured, not modelled): every block length
  * first, then the split count and the chunk at the best one, then column
  * tiles instead of the blocked convolution if the problems have narrow
- * groups.  Stops starting new trials once budget_s seconds have passed (the
- * block-length stage always runs at least one).  Device memory for one plan
+ * groups.  One trajectory in double is first tried without a blocking (all
+ * zeros, see abm_solve_batch).  Stops starting new trials once budget_s
+ * seconds have passed (at least one always runs).  Device memory for one plan
  * at a time plus scratch outputs.  best receives the fastest configuration,
  * where a trial replaces an earlier, slower one only if it is more than 2%
  * faster (so that run-to-run noise does not decide); trials (may be NULL)
@@ -228,10 +231,13 @@ abm_status abm_solve(abm_plan_t *plan, const abm_problem *prob, double *y_out);
  * of L steps enters through a Toeplitz-weight x history product on the matrix
  * cores, the last steps through a near band kept on chip, and the sequential
  * predictor/corrector runs per trajectory in double.  A single trajectory
- * with the double far field that abm_solve accepts runs as abm_solve does
- * (unless the plan is for column tiles only): stats then count one chain
- * launch and no far-field work.  y_out is a host array of B device pointers,
- * each sized as for abm_solve.  stats may be NULL.
+ * with the double far field that abm_solve accepts runs as abm_solve does,
+ * unless the plan was given a blocking (abm_tuning or the environment) or is
+ * for column tiles only.  far_launches is then 0 and chain_launches 1
+ * (narrow_groups still counts the plan's group), abm_plan_config is all zeros
+ * and abm_plan_graph without effect, and results differ by rounding from the
+ * blocked method's.  y_out is a host array of B device pointers, each sized as
+ * for abm_solve.  stats may be NULL.
  * Errors: ABM_EINVAL, ABM_EDEVICE. */
 abm_status abm_solve_batch(abm_plan_t *plan, const abm_problem *probs, int32_t B,
                            double *const *y_out, abm_stats *stats);

@@ -115,6 +115,8 @@ struct abm_plan_s {
     // blocked path: groups and their static tick schedule
     abm_tuning tune{};            // requested blocking (zero fields: defaults)
     bool allow_narrow = true;
+    bool blocking_given = false;  // by the caller or the environment
+    bool single_plain = false;    // abm_solve_batch of one trajectory runs as abm_solve
     int L = 0;
     int kchunk = 0;
     int kchunk64 = 0;             // chunk rows of the double column tiles

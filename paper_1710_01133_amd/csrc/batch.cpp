@@ -356,6 +356,8 @@ static abm_status choose_blocking(abm_plan_s* pl, const abm_problem* probs, int 
     pl->max_split = T.max_split ? T.max_split : env_int("ABM_MAX_SPLIT", 8);
     if (pl->max_split < 1 || pl->max_split > 4096)
         return fail(ABM_EINVAL, "split count %d out of range 1..4096", pl->max_split);
+    pl->blocking_given = T.block_L || T.kchunk || T.max_split || env_int("ABM_BLOCK_L", 0) ||
+                         env_int("ABM_KCHUNK", 0) || env_int("ABM_MAX_SPLIT", 0);
     pl->allow_narrow = !T.column_tiles_only && env_int("ABM_NARROW", 1) != 0;
     return ABM_OK;
 }
@@ -594,6 +596,13 @@ static abm_status batch_build(abm_plan_s* pl, bool transforms)
         e = hipStreamCreateWithFlags(&pl->far_stream, hipStreamNonBlocking);
         if (e != hipSuccess) return hip_fail(e, "far stream");
     }
+    // One trajectory in double whose history fits the workgroups of abm_solve
+    // runs there: the blocked convolution of a lone narrow group takes two or
+    // three launches per 256 steps and its one chain wave shares the chip with
+    // them (N = 8192 linear 0.19 us per step, 10^6 steps of the oscillator
+    // 0.31; abm_solve 0.065 and 0.14).  A blocking that was asked for is used.
+    const Group& g0 = pl->groups[0];
+    pl->single_plain = pl->B == 1 && pl->plain_ok && !pl->blocking_given && g0.narrow && g0.prec == ABM_FAR_FP64;
     return ABM_OK;
 }
 
@@ -855,12 +864,7 @@ extern "C" abm_status abm_solve_batch(abm_plan_t* pl, const abm_problem* probs, 
     for (const Group& g : pl->groups) S.narrow_groups += g.narrow ? 1 : 0;
     S.far_macs = pl->far_macs;
 
-    // One trajectory in double whose history fits the workgroups of abm_solve
-    // runs there: the blocked convolution of a lone narrow group takes two or
-    // three launches per 256 steps and its one chain wave shares the chip with
-    // them (N = 8192 linear 0.19 us per step, 10^6 steps of the oscillator
-    // 0.31; abm_solve 0.065 and 0.14).  A plan made for column tiles keeps them.
-    if (B == 1 && pl->plain_ok && pl->groups[0].narrow && pl->groups[0].prec == ABM_FAR_FP64) {
+    if (pl->single_plain) {
         S.history_macs = (int64_t)probs[0].d * probs[0].N * (probs[0].N + 1) / 2;
         S.chain_launches = 1;
         hipEvent_t ev[2] = {nullptr, nullptr};
@@ -958,6 +962,8 @@ extern "C" abm_status abm_plan_timing(abm_plan_t* pl, int32_t enable)
 extern "C" abm_status abm_plan_config(abm_plan_t* pl, abm_tuning* out)
 {
     if (!pl || !out) return fail(ABM_EINVAL, "NULL argument");
+    *out = abm_tuning{};
+    if (pl->single_plain) return ABM_OK;   // no blocking in use
     out->block_L = pl->L;
     out->kchunk = pl->kchunk;
     out->max_split = pl->max_split;

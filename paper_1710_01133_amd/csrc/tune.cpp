@@ -129,11 +129,14 @@ extern "C" abm_status abm_autotune(abm_ctx* ctx, const abm_problem* probs, int32
 
     const double t0 = wall_s();
     auto in_budget = [&]() { return wall_s() - t0 < budget_s; };
+    // one trajectory in double: first as the library runs it when no blocking
+    // is given, which for most lengths is abm_solve's kernel
+    if (B == 1 && all_fp64) (void)T.run(abm_tuning{});
     // stage 1: block length (always at least one trial)
     std::vector<int> Ls = {256, 128, 512};
     if (all_fp64) Ls.push_back(64);
     for (size_t i = 0; i < Ls.size(); ++i) {
-        if (i > 0 && !in_budget()) break;
+        if (!T.trials.empty() && !in_budget()) break;
         abm_tuning c{};
         c.block_L = Ls[i];
         (void)T.run(c);
@@ -142,9 +145,10 @@ extern "C" abm_status abm_autotune(abm_ctx* ctx, const abm_problem* probs, int32
     // win by the margin), stage 3: chunk, at the best so far, where column
     // tiles read it (double ones sum at most a superblock of 2048 rows)
     const int splits[] = {2, 4, 16};
+    auto unblocked = [&]() { return T.best() && T.best()->cfg.block_L == 0; };   // nothing to refine
     for (int sp : splits) {
         const abm_tune_trial* b = T.best();
-        if (!b || !in_budget()) break;
+        if (!b || unblocked() || !in_budget()) break;
         abm_tuning c = b->cfg;
         c.max_split = sp;
         (void)T.run(c);
@@ -153,14 +157,14 @@ extern "C" abm_status abm_autotune(abm_ctx* ctx, const abm_problem* probs, int32
                                              : std::vector<int>{1024, 4096, 8192};
     for (int kc : chunks) {
         const abm_tune_trial* b = T.best();
-        if (!b || !in_budget() || T.tiles[b - T.trials.data()] == 0) break;
+        if (!b || unblocked() || !in_budget() || T.tiles[b - T.trials.data()] == 0) break;
         abm_tuning c = b->cfg;
         c.kchunk = kc;
         (void)T.run(c);
     }
     // stage 4: column tiles for every group instead of the blocked convolution
     if (const abm_tune_trial* b = T.best()) {
-        if (in_budget() && T.narrow[b - T.trials.data()] > 0) {
+        if (in_budget() && !unblocked() && T.narrow[b - T.trials.data()] > 0) {
             abm_tuning c = b->cfg;
             c.column_tiles_only = 1;
             (void)T.run(c);
