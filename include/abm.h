@@ -236,7 +236,11 @@ abm_status abm_solve(abm_plan_t *plan, const abm_problem *prob, double *y_out);
  * for column tiles only.  far_launches is then 0 and chain_launches 1
  * (narrow_groups still counts the plan's group), abm_plan_config is all zeros
  * and abm_plan_graph without effect, and results differ by rounding from the
- * blocked method's.  y_out is a host array of B device pointers, each sized as
+ * blocked method's.  That form's workgroups wait for each other and, for long
+ * trajectories, take every CU until the end; where something else holds part
+ * of the GPU past the bound on those waits (a few seconds), the trajectory is
+ * taken again by at most 17 workgroups.  A process that shares its GPU and
+ * wants neither gives the plan a blocking.  y_out is a host array of B device pointers, each sized as
  * for abm_solve.  stats may be NULL.
  * Errors: ABM_EINVAL, ABM_EDEVICE. */
 abm_status abm_solve_batch(abm_plan_t *plan, const abm_problem *probs, int32_t B,

@@ -377,7 +377,7 @@ abm_status abm_solve(abm_plan_t* pl, const abm_problem* prob, double* y_out)
         return fail(ABM_EINVAL, "problem does not match the plan (rhs, d, orders, N, far_prec, out_stride)");
     hipError_t e = hipSetDevice(pl->ctx->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
-    e = plain_run(pl, *prob, y_out);
+    e = plain_run(pl, *prob, y_out, false);
     if (e != hipSuccess) return hip_fail(e, "plain kernel launch");
     return ABM_OK;
 }
@@ -398,6 +398,20 @@ namespace abm {
 // 1.056 / 1.058; 2048 steps: 0.595 / 0.445 and 1.249 / 1.037).
 constexpr int kAloneBlocks = 32, kAloneBlocksDd = 16;
 constexpr int kWorkerChunks = 16;
+
+// what W workers and nred reducers keep
+static void size_workers(const abm_problem& p, PlainShape* sh)
+{
+    const bool dd = p.far_prec == ABM_FAR_DD;
+    const size_t chunk = (size_t)p.d * kPlainBlock * (dd ? 2 : 1), slot = 2 * chunk;
+    const int64_t chunks = (p.N + kPlainBlock - 1) / kPlainBlock;
+    const int64_t each = (chunks + sh->W - 1) / sh->W;
+    sh->nloc = (int)std::min<int64_t>(each, dd ? plain_dd_worker_chunks(p.d) : plain_worker_chunks(p.d));
+    sh->nspill = (int)(each - sh->nloc);
+    sh->work_doubles = kPlainRing * chunk + kPlainSlots * (size_t)(sh->nred + sh->W) * slot +
+                       (size_t)sh->W * sh->nspill * chunk;
+    sh->flags = kPlainFlagPad + sh->W + sh->nred;
+}
 
 abm_status plain_shape(const abm_problem& p, int n_cu, PlainShape* out)
 {
@@ -429,15 +443,18 @@ abm_status plain_shape(const abm_problem& p, int n_cu, PlainShape* out)
     others = std::min(others, gcap - 1);
     sh.nred = others <= kPlainFan ? 0 : (others + kPlainFan) / (kPlainFan + 1);
     sh.W = others - sh.nred;
-    const int64_t each = (chunks + sh.W - 1) / sh.W;
-    sh.nloc = (int)std::min<int64_t>(each, dd ? plain_dd_worker_chunks(d) : plain_worker_chunks(d));
-    sh.nspill = (int)(each - sh.nloc);
-    const size_t slot = (size_t)2 * d * kPlainBlock * words, chunk = (size_t)d * kPlainBlock * words;
-    sh.work_doubles = kPlainRing * chunk + kPlainSlots * (size_t)(sh.nred + sh.W) * slot +
-                      (size_t)sh.W * sh.nspill * chunk;
-    sh.flags = kPlainFlagPad + sh.W + sh.nred;
+    size_workers(p, &sh);
     *out = sh;
     return ABM_OK;
+}
+
+PlainShape plain_shape_small(const abm_problem& p, const PlainShape& full)
+{
+    PlainShape sh = full;
+    sh.W = std::min(full.W, kPlainFan);
+    sh.nred = 0;
+    size_workers(p, &sh);
+    return sh;
 }
 
 PlainArgs plain_args(const abm_problem& prob, const PlainTables& T, const PlainShape& sh,
@@ -489,7 +506,11 @@ hipError_t plain_enqueue(const PlainArgs& A, const PlainShape& sh, int kind, boo
     return dd ? launch_plain_dd(A, kind, st) : launch_plain(A, kind, st);
 }
 
-hipError_t plain_run(abm_plan_s* pl, const abm_problem& prob, double* y_out)
+// flags of a plan: the run's, the status word of a run that may be repeated,
+// the repeated run's
+static size_t flag_words(const abm_plan_s* pl) { return pl->plain.flags + 1 + pl->again.flags; }
+
+hipError_t plain_run(abm_plan_s* pl, const abm_problem& prob, double* y_out, bool retry)
 {
     PlainTables T{};
     for (int i = 0; i < 4; ++i) {
@@ -500,8 +521,28 @@ hipError_t plain_run(abm_plan_s* pl, const abm_problem& prob, double* y_out)
         T.gam[i] = t.gam;
         T.alpha[i] = t.alpha;
     }
-    const PlainArgs A = plain_args(prob, T, pl->plain, pl->part, pl->flags, pl->status, y_out);
-    return plain_enqueue(A, pl->plain, chain_kind(prob.rhs, orders_differ(prob)), pl->dd, pl->ctx->stream);
+    const hipStream_t st = pl->ctx->stream;
+    const int kind = chain_kind(prob.rhs, orders_differ(prob));
+    if (!retry || pl->plain.W == 0) {
+        const PlainArgs A = plain_args(prob, T, pl->plain, pl->part, pl->flags, pl->status, y_out);
+        return plain_enqueue(A, pl->plain, kind, pl->dd, st);
+    }
+    // The workgroups of the first run wait for each other and so need the chip
+    // to themselves; where another process holds part of it past the bound on
+    // the waits, they give up.  The second launch then takes the trajectory
+    // again with at most kPlainFan workers, which up to 15 such processes can
+    // hold side by side, and waits longer (oscillator, 200000 steps 50 ms for
+    // 20, 10^6 steps 1.2 s for 0.14).  Otherwise it returns at once.
+    uint32_t* const first = pl->flags + pl->plain.flags;
+    hipError_t e = launch_fill_u32(pl->flags, 0, flag_words(pl), st);
+    if (e != hipSuccess) return e;
+    PlainArgs A = plain_args(prob, T, pl->plain, pl->part, pl->flags, first, y_out);
+    if ((e = launch_plain(A, kind, st)) != hipSuccess) return e;
+    A = plain_args(prob, T, pl->again, pl->part, first + 1, pl->status, y_out);
+    A.gate = first;
+    A.spin_limit = 8 * kSpinLimit;
+    A.wait_bias = 0;
+    return launch_plain(A, kind, st);
 }
 
 abm_status plain_setup(abm_plan_s* pl)
@@ -510,8 +551,14 @@ abm_status plain_setup(abm_plan_s* pl)
     if (st != ABM_OK) return st;
     const PlainShape& sh = pl->plain;
     if (sh.W > 0) {
-        st = dev_alloc((void**)&pl->part, sh.work_doubles * sizeof(double), "plain workspace");
-        if (st == ABM_OK) st = dev_alloc((void**)&pl->flags, sh.flags * sizeof(uint32_t), "plain flags");
+        // (the second run reuses the first one's workspace)
+        size_t work = sh.work_doubles;
+        if (pl->shape[0].far_prec == ABM_FAR_FP64) {
+            pl->again = plain_shape_small(pl->shape[0], sh);
+            work = std::max(work, pl->again.work_doubles);
+        }
+        st = dev_alloc((void**)&pl->part, work * sizeof(double), "plain workspace");
+        if (st == ABM_OK) st = dev_alloc((void**)&pl->flags, flag_words(pl) * sizeof(uint32_t), "plain flags");
     }
     pl->plain_ok = st == ABM_OK;
     return st;

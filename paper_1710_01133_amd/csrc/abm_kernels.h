@@ -67,6 +67,8 @@ struct PlainArgs {
     double* y_out;
     int64_t out_stride;
     uint32_t* status;    // device status word (kStatus* bits)
+    const uint32_t* gate;   // null, or the status word of a run before this one: this one then
+                         // runs only if a wait of that one gave up, else it hands its bits on
     uint32_t spin_limit; // bound on each device-side wait
     uint32_t wait_bias;  // added to every awaited number: 0 (a test hook
                          // sets it so that no wait can be met)
@@ -76,7 +78,7 @@ struct PlainArgs {
 size_t plain_chain_lds(int d, bool per_comp, int64_t chunks, bool alone);
 int plain_worker_chunks(int d);
 // kind: chain_kind(rhs, components have their own orders).  One cooperative
-// launch (an ordinary one if A.W = 0); flags zero.
+// launch (an ordinary one if A.W = 0 or behind a gate); flags zero.
 hipError_t launch_plain(const PlainArgs& A, int kind, hipStream_t st);
 
 // ---- K0 / K1 in double-double (ABM_FAR_DD) -----------------------------------

@@ -107,6 +107,7 @@ struct abm_plan_s {
     // plain path (B == 1)
     bool plain_ok = false;
     abm::PlainShape plain{};
+    abm::PlainShape again{};      // abm_solve_batch's second run if a wait of the first gives up
     bool dd = false;              // double-double plan (ABM_FAR_DD): plain path only, tables
                                   // of (hi, lo) pairs
     std::string plain_error;
@@ -180,12 +181,15 @@ struct PlainTables {
 };
 // (far_prec of p: double, or double-double)
 abm_status plain_shape(const abm_problem& p, int n_cu, PlainShape* out);
+// ... with at most kPlainFan workers and no reducers, for histories that take several workgroups
+PlainShape plain_shape_small(const abm_problem& p, const PlainShape& sh);
 PlainArgs plain_args(const abm_problem& prob, const PlainTables& T, const PlainShape& sh,
                      double* work, uint32_t* flags, uint32_t* status, double* y_out);
 // flags reset and the kernel, on st
 hipError_t plain_enqueue(const PlainArgs& A, const PlainShape& sh, int kind, bool dd, hipStream_t st);
-// the one trajectory of a plan with B = 1 (plain_ok) on the context's stream
-hipError_t plain_run(abm_plan_s* pl, const abm_problem& prob, double* y_out);
+// the one trajectory of a plan with B = 1 (plain_ok) on the context's stream;
+// retry: once more in a smaller shape if a wait gave up
+hipError_t plain_run(abm_plan_s* pl, const abm_problem& prob, double* y_out, bool retry);
 abm_status plain_setup(abm_plan_s* pl);
 abm_status batch_setup(abm_plan_s* pl);
 void batch_teardown(abm_plan_s* pl);

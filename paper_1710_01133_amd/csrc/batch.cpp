@@ -878,7 +878,7 @@ extern "C" abm_status abm_solve_batch(abm_plan_t* pl, const abm_problem* probs, 
             ev[1] = pl->events[1];
             if ((e = hipEventRecord(ev[0], st)) != hipSuccess) return hip_fail(e, "timing event");
         }
-        if ((e = plain_run(pl, probs[0], y_out[0])) != hipSuccess) return hip_fail(e, "plain kernel launch");
+        if ((e = plain_run(pl, probs[0], y_out[0], true)) != hipSuccess) return hip_fail(e, "plain kernel launch");
         if (pl->timing) {
             float ms = 0.f;
             if ((e = hipEventRecord(ev[1], st)) != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess ||

@@ -763,6 +763,13 @@ __global__ __launch_bounds__(kThreads) void k_plain(PlainArgs A)
     extern __shared__ __align__(16) double lds[];
     __shared__ uint32_t s_abort;
     T* sm = reinterpret_cast<T*>(lds);
+    if (A.gate) {
+        const uint32_t bits = ld_relaxed(A.gate);
+        if (!(bits & kStatusTimeout)) {
+            if (bits && blockIdx.x == 0 && threadIdx.x == 0) raise_status(A.status, bits);
+            return;
+        }
+    }
     if (threadIdx.x == 0) s_abort = 0;
     __syncthreads();
     const int g = blockIdx.x;
@@ -794,8 +801,8 @@ hipError_t launch(const PlainArgs& A, hipStream_t st)
     const void* fn = reinterpret_cast<const void*>(&k_plain<T, R, D, PC>);
     hipError_t e = allow_lds(fn, shmem);
     if (e != hipSuccess) return e;
-    if (A.W == 0) {
-        hipLaunchKernelGGL((k_plain<T, R, D, PC>), dim3(1), dim3(kThreads), shmem, st, A);
+    if (A.W == 0 || A.gate) {
+        hipLaunchKernelGGL((k_plain<T, R, D, PC>), dim3(1 + A.W + A.nred), dim3(kThreads), shmem, st, A);
         return hipGetLastError();
     }
     PlainArgs a = A;
