@@ -440,10 +440,16 @@ abm_status plain_shape(const abm_problem& p, int n_cu, PlainShape* out)
         const int W = (int)std::min<int64_t>((chunks + kWorkerChunks - 1) / kWorkerChunks, gcap);
         others = W <= kPlainFan ? W : W + (W + kPlainFan - 1) / kPlainFan;
     }
-    others = std::min(others, gcap - 1);
-    sh.nred = others <= kPlainFan ? 0 : (others + kPlainFan) / (kPlainFan + 1);
-    sh.W = others - sh.nred;
-    size_workers(p, &sh);
+    others = std::max(1, std::min(others, gcap - 1));
+    for (;; ++others) {
+        // every reducer with workers of its own (18 others are 16 workers and none)
+        sh.W = others <= kPlainFan ? others : others - (others + kPlainFan) / (kPlainFan + 1);
+        sh.nred = sh.W <= kPlainFan ? 0 : (sh.W + kPlainFan - 1) / kPlainFan;
+        size_workers(p, &sh);
+        // a forced count is raised until what its workers spill fits the
+        // slots of abm_solve_noalloc, which takes the shape as it is
+        if (forced <= 0 || sh.work_doubles * sizeof(double) <= kPlainSlotBytes || others >= gcap - 1) break;
+    }
     *out = sh;
     return ABM_OK;
 }

@@ -31,6 +31,7 @@ constexpr int kPlainSlots = 4;     // partial slots per worker, by block mod kPl
 constexpr int kPlainFan = 16;      // partials summed by one workgroup
 constexpr int kPlainRing = 8;      // published chunks kept
 constexpr int kPlainFlagPad = 32;  // flags[0]: workgroup 0's progress; the workers' flags start here
+constexpr size_t kPlainSlotBytes = (size_t)4 << 20;   // abm_solve_noalloc's array of slots
 constexpr size_t kPlainLds = 160 * 1024 - 256;   // LDS of one gfx950 CU, less the static flag
 
 // Launch shape: workgroup 0 steps, W workers hold the history (0: workgroup 0

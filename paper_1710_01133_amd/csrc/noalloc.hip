@@ -33,7 +33,7 @@ constexpr size_t kScratchBytes = (size_t)8 << 20;
 constexpr size_t kStatusOff = 0;
 constexpr size_t kFlagsOff = 256;
 constexpr size_t kTablesOff = 1280 + 128 * 1024;   // the stated limit on N follows from it
-constexpr size_t kSlotBytes = (size_t)4 << 20;     // 256 workgroups' slots of three components
+constexpr size_t kSlotBytes = kPlainSlotBytes;     // 256 workgroups' slots of three components
 constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
