@@ -221,7 +221,10 @@ abm_status abm_autotune(abm_ctx *ctx, const abm_problem *probs, int32_t B, doubl
  * over workgroups that each own a fixed slice of it (the partition of
  * Algorithm 1).  The reduction over them is taken once per block of 64 steps:
  * one workgroup steps, adding the newest two blocks' terms itself, and
- * receives the slices' sums of older history a block ahead.
+ * receives the slices' sums of older history a block ahead.  At most 2.55e6
+ * steps of two components on 256 CUs, 1.24e6 in double-double (three: 1.70e6
+ * and 8.5e5; one: 5.1e6 and 2.5e6): longer plans have no plain path
+ * (ABM_EINVAL here; in double-double from abm_plan).
  * y_out: device pointer to n_out*d doubles, n_out = 1 (stride 0) or
  * N/stride + 1 (+1 if stride does not divide N), states in step order.
  * Errors: ABM_EINVAL (prob does not match the plan), ABM_EDEVICE. */

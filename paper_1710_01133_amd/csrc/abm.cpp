@@ -419,13 +419,16 @@ abm_status plain_shape(const abm_problem& p, int n_cu, PlainShape* out)
     const bool dd = p.far_prec == ABM_FAR_DD;
     const int words = dd ? 2 : 1;
     const int gcap = std::min(n_cu, 256);      // one workgroup per CU is always resident
-    // the longest history accepted: 256-row pieces in the LDS of gcap
-    // workgroups, less a fixed part
+    // The longest history accepted, as many 256-row pieces as the LDS of gcap
+    // workgroups could hold less a fixed part: 2.55e6 steps of two components
+    // on 256 CUs, 1.24e6 in double-double.  Workers keep fewer (119 chunks of
+    // 64 rows, 39 in double-double: 1.8e6 and 6e5 steps) and spill the rest to
+    // device memory.
     const size_t fixed = dd ? (size_t)1216 * d : (size_t)512 * d;
     const int64_t rows_max = (int64_t)gcap * 256 * ((kPlainLds - fixed) / ((size_t)2048 * d * words));
     if ((p.N + 255) / 256 * 256 > rows_max)
-        return fail(ABM_EINVAL, "N=%lld too long for the %splain path (history does not fit the LDS of %d workgroups)",
-                    (long long)p.N, dd ? "double-double " : "", gcap);
+        return fail(ABM_EINVAL, "N=%lld too long for the %splain path (at most %lld steps of %d components on %d CUs)",
+                    (long long)p.N, dd ? "double-double " : "", (long long)rows_max, d, gcap);
     const bool pc = orders_differ(p);
     const int64_t chunks = (p.N + kPlainBlock - 1) / kPlainBlock;
     const int forced = env_int("ABM_PLAIN_G", 0);
