@@ -40,6 +40,10 @@ constexpr int kThreads = 256, kPts = NF / kThreads;
 constexpr int kRow1 = 272, kRow2 = 17;       // padded rows of the two exchanges (doubles)
 constexpr int kLds = 16 * kRow1;             // 4352 doubles; 256 * kRow2 = 4352
 static_assert(kPts == 16 && NF == 16 * 16 * 16, "three radix-16 passes");
+// 1 / NF, taken at the front so that no value between exceeds what the direct
+// products would form: 2^-11 from the history (a sum of S values), the rest
+// from the weights.  Powers of two: nothing else changes.
+constexpr double kScaleF = 1.0 / S, kScaleW = (double)S / NF;
 
 struct cplx {
     double re, im;
@@ -181,7 +185,7 @@ __global__ __launch_bounds__(kThreads) void k_fft_weights(const double* b, const
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
         const int i = v + 256 * e;
-        x[e] = {i < NF - 1 && at + i < n ? w[at + i] : 0.0, 0.0};
+        x[e] = {i < NF - 1 && at + i < n ? kScaleW * w[at + i] : 0.0, 0.0};
     }
     fft(x, v, v, lds, as_global(tw));
     store_half(x, v, as_global(out) + ((size_t)blockIdx.x * 2 + blockIdx.y) * kFftStride);
@@ -203,7 +207,7 @@ __global__ __launch_bounds__(kThreads) void k_fft_history(const GroupDev* groups
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
         const int64_t k = k0 + v + 256 * e;
-        x[e] = {e < 8 && k >= 1 ? F[k * G.ldF] : 0.0, 0.0};
+        x[e] = {e < 8 && k >= 1 ? kScaleF * F[k * G.ldF] : 0.0, 0.0};
     }
     fft(x, v, v, lds, as_global(tw));
     store_half(x, v, as_global((cplx*)G.spec) + ((size_t)(it.Q - 1) * G.ldF + col) * kFftStride);
@@ -275,13 +279,12 @@ __global__ __launch_bounds__(kThreads) void k_fft_sums(const GroupDev* groups, c
         __syncthreads();
     }
     fft(x, lo, v, lds, as_global(tw));
-    // element n = low + 256 j of conj(result) NF; rows r = n - (S - 1)
+    // element n = low + 256 j of conj(result); rows r = n - (S - 1)
     const gptr<double> out = as_global(G.fpart) + (size_t)(it.Q & 1) * (S / L) * G.ldF * (2 * L);
 #pragma unroll
     for (int part = 0; part < 2; ++part) {
-        const double scale = part == 0 ? 1.0 / NF : -1.0 / NF;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) lds[lo + 256 * j] = scale * (part == 0 ? x[j].re : x[j].im);
+        for (int j = 0; j < 16; ++j) lds[lo + 256 * j] = part == 0 ? x[j].re : -x[j].im;
         __syncthreads();
 #pragma unroll
         for (int e = 0; e < S / kThreads; ++e) {
