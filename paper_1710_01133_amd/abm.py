@@ -299,7 +299,7 @@ def alloc_out(problem: Problem, out_stride: int, device: str = "cuda"):
 
 
 def solve(plan: Plan, problem: Problem, y_out) -> None:
-    """Plain per-step path (plan over one problem).  y_out: float64 device tensor."""
+    """Plain path (plan over one problem).  y_out: float64 device tensor."""
     c = c_problem(problem, plan.out_stride)
     _check(load().abm_solve(plan.handle, ctypes.byref(c), ctypes.c_void_p(y_out.data_ptr())),
            "abm_solve")

@@ -23,13 +23,16 @@
 //     reducer workgroup each; workgroup 0 sums the at most kFan results.
 // What bounds it: the sequencer's instructions (one wave; an f64 operation
 // issues every 4.2 cycles whether or not it depends on the one before, and so
-// does every other instruction), 0.053 us per step for the linear equation,
-// 0.100 for the oscillator, 0.138 for Lorenz, at any length (double-double:
-// 0.43, 1.02, 1.43); one reduction per step took 0.91 (8192 steps of the linear
-// equation, one workgroup) and 2.9 (200000 steps of the oscillator;
-// double-double 2.4 and 5.0).  Hence the 64 rows unrolled (a lane index
-// in an SGPR costs a readlane twice the time: 0.135 us per step of the
-// oscillator with a rolled loop) and the weights read one group of rows ahead.
+// does every other instruction), 0.053 us per step for the linear equation
+// (0.065 with every state written), 0.098 for the oscillator, 0.138 for Lorenz,
+// 0.169 for the circuit, from a few thousand steps on (double-double: 0.43,
+// 1.02, 1.41, 1.23).  Beyond about 5e5 steps the workers' weights come from
+// beyond L2 (10^6 steps of the oscillator: 0.139).  One reduction per step took
+// 0.91 (8192 steps of the linear equation, one workgroup) and 2.9 (200000 steps
+// of the oscillator; double-double 2.4 and 5.0).  Hence the 64 rows unrolled
+// (a lane index in an SGPR costs a readlane twice the time: 0.135 us per step
+// of the oscillator with a rolled loop) and the weights read one group of rows
+// ahead.
 // Every sum is taken in an order fixed by (N, W) alone.  Short histories run
 // in workgroup 0 alone (W = 0): the waves beside the sequencer then sum the
 // chunks c <= q - 2 from LDS while block q - 1 runs.
@@ -230,9 +233,9 @@ __device__ __forceinline__ void chunk_mac(const Weight<T>* win, const T* Fc, int
 // moves instead of shuffles (two trips through the LDS unit per double, and
 // four selects) took the linear system of 8192 steps from 536 to 528 us, the
 // oscillator of 200000 from 20.1 to 19.8 ms and of 10^6 from 145.9 to 140.0;
-// in double-double 3.91 to 3.48 ms for one component.  Two components there
-// measured slower with the moves (100000 steps 100.0 against 112.6 ms: the
-// rolled loop of the sequencer is scheduled worse around them), so they shuffle.
+// in double-double 3.91 to 3.48 ms for one component.  Two and three
+// components there shuffle: no slower for two (1.017 us per step either way)
+// and faster for three (Lorenz 1.407 against 1.420).
 template <class T, int D>
 __device__ __forceinline__ void group_sum(T (&acc)[kB / Num<T>::LR][2][D], int lane, T* out)
 {
