@@ -25,11 +25,12 @@
 // What bounds it: reading the spectra, S + 1 complex values per history block
 // and column -- in the sweep of 1024 oscillators over 65536 steps 1.15 GB a
 // launch on average, 328 us, 3.5 TB/s (a large copy: 5.5); of it about 50 us
-// are bank conflicts where the sums leave through LDS.  One column per workgroup of 256 threads, 16 points per
-// thread, three radix-16 passes exchanged through 35 KB of LDS, four
-// workgroups to a CU.  S = 2048: of 4096 points a pass is 16 per thread and
-// 4096 = 16^3; half of it doubles the spectra read, twice of it leaves one
-// workgroup per CU and doubles the direct part.
+// are bank conflicts where the sums leave through LDS.  One column per
+// workgroup of 256 threads, 16 points per thread, three radix-16 passes
+// exchanged through 35 KB of LDS, four workgroups to a CU.  S = 2048: of 4096
+// points a pass is 16 per thread and 4096 = 16^3; half of it doubles the
+// spectra read, twice of it leaves one workgroup per CU and doubles the direct
+// part.
 #include "abm_dev.h"
 #include "abm_kernels.h"
 
