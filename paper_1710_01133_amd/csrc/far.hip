@@ -144,14 +144,16 @@ __global__ __launch_bounds__(256, 2) void k_far_f64(const GroupDev* groups, cons
         }
     }
 
-    // The first slice also takes the sums of the transforms over the history
-    // before this superblock (their columns are the group's).  Read by the
-    // chains instead, they cost every other precision's chains a branch and
-    // registers: circuit sweep in int8 limbs 106.5 against 105.8 ms.
+    // The last slice also takes the sums of the transforms over the history
+    // before this superblock (their columns are the group's): the largest
+    // term, so that the chains, which add the slices in order, round at its
+    // size once.  Read by the chains instead, they cost every other
+    // precision's chains a branch and registers: circuit sweep in int8 limbs
+    // 106.5 against 105.8 ms.
     const FarItem it = items[blockIdx.z];
     const int64_t Q = mL / kFftRows;
     const double* const sums = groups[it.group].fpart;
-    const bool add = sums && Q > 0 && blockIdx.y == 0;
+    const bool add = sums && Q > 0 && (int)blockIdx.y == it.nsplit - 1;
     const int64_t block = (Q & 1) * (kFftRows / L) + (mL - Q * kFftRows) / L;
     const gptr<const double> old =
         add ? as_global(sums) + ((size_t)block * A.ldF + it.coff) * (2 * L) : nullptr;
